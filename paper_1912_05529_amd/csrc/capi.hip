@@ -555,7 +555,7 @@ MIG_API size_t mig_design_workspace_size(const mig_table_desc* d)
     const size_t K = (size_t)(d->ntaps - 1) / 2 + 1;
     return align_up((size_t)d->ngrid * K * sizeof(double), kAlign) +
            align_up((size_t)d->ncheck * K * sizeof(double), kAlign) +
-           align_up((size_t)d->nk * sizeof(int), kAlign);
+           align_up((size_t)d->nk * sizeof(int), kAlign) + design_target_bytes(d);
 }
 
 MIG_API int mig_design_table(const mig_table_desc* d, mig_c128* tab64, mig_c64* tab32,
@@ -575,9 +575,10 @@ MIG_API int mig_design_table(const mig_table_desc* d, mig_c128* tab64, mig_c64* 
     double* C = reinterpret_cast<double*>(p);
     p += align_up((size_t)d->ncheck * K * sizeof(double), kAlign);
     int* status = reinterpret_cast<int*>(p);
+    p += align_up((size_t)d->nk * sizeof(int), kAlign);
 
     int rc = launch_design_basis(d, A, C, s);
-    if (rc == MIG_OK) rc = launch_design(d, A, C, tab64, tab32, maxgain, passerr, status, s);
+    if (rc == MIG_OK) rc = launch_design(d, A, C, p, tab64, tab32, maxgain, passerr, status, s);
     if (rc != MIG_OK) return rc;
     if (hipStreamSynchronize(s) != hipSuccess) return MIG_E_DEVICE;
     int worst = 0;

@@ -192,7 +192,9 @@ int threads_per_omega(int kind, int nx);
 
 // Host launchers (return MIG_OK or MIG_E_DEVICE).
 int launch_design_basis(const mig_table_desc* d, double* A, double* C, hipStream_t s);
-int launch_design(const mig_table_desc* d, const double* A, const double* C,
+// Target values of the entries in flight, in the workspace (1-D design).
+size_t design_target_bytes(const mig_table_desc* d);
+int launch_design(const mig_table_desc* d, const double* A, const double* C, void* targets,
                   mig_c128* tab64, mig_c64* tab32, double* maxgain,
                   double* passerr, int* status, hipStream_t s);
 int launch_index(const float* vel, const double* omega, int nx, int nw,

@@ -9,155 +9,43 @@
 // and a final scale that bounds |H| below one for every wavenumber (Bernstein's
 // inequality for trigonometric polynomials).  The formulas are in mig.h.
 //
-// Mapping: one workgroup per entry.  The grid quantities (weights, target) live
-// in LDS; the basis matrices (design grid and check grid, shared by all
-// entries) are computed once into the workspace and read through L2.  Each
-// entry of the normal matrix is accumulated by one thread over the grid in
-// increasing grid order, and the Cholesky solve runs on one thread: the design
-// is a few thousand flops per entry per pass, far from any roofline, and a
-// fixed sequential order keeps the result reproducible.
+// Mapping (k_design, both dimensions): a workgroup designs EB = 1 or 2 entries.  What
+// costs is the normal matrix: K (K+1) / 2 + 2 K sums over the design grid, 31 times per
+// entry.  Each sum runs over the grid in increasing order (another order moves the
+// fitted table by 1e-10: the fit's conditioning), so a sum is one thread's; a thread
+// owns a 2 x 2 tile of them for all EB entries, which share the basis rows: per grid
+// point 4 basis values and a weight per entry from LDS for 10 operations per entry.
+// The basis streams through LDS in chunks of 64 grid points; the response |H| that
+// reweights a point is evaluated from the same chunk, just before the chunk is summed.
+// The system is solved by one wave (or half of one) per entry: a row per lane in
+// registers, one LDS exchange of the current column per elimination step, the
+// right-hand sides as two more rows.
 #include "common.hpp"
 
 namespace mig {
 namespace {
 
-constexpr int kDesignThreads = 256;
-constexpr int kMaxK = MIG_MAX_NTAPS / 2 + 1;  // 32
+constexpr int kMaxM2 = MIG_MAX_NTAPS_2D / 2;      // 5
+constexpr int kDesignMaxSlots = 2048;         // entries in flight (1-D: target values in the workspace)
 
-// A[i][n] = 1 (n = 0) or 2 cos(n theta_i) on the design midpoint grid;
-// C[c][n] likewise on the check grid.
-__global__ void k_design_basis(int L, int Lc, int K, double* A, double* C)
+// A[i][n] = 1 (n = 0) or 2 cos(n theta_i) on the design midpoint grid; Ct[n][c]
+// likewise on the check grid, point fastest.
+__global__ void k_design_basis(int L, int Lc, int K, double* A, double* Ct)
 {
 #pragma clang fp contract(off)
     int tid = blockIdx.x * blockDim.x + threadIdx.x;
     int total = (L + Lc) * K;
     for (int e = tid; e < total; e += gridDim.x * blockDim.x) {
-        int i = e / K, n = e % K;
-        if (i < L) {
+        if (e < L * K) {
+            const int i = e / K, n = e % K;
             double th = ((double)i + 0.5) * kPi / (double)L;
-            A[(size_t)i * K + n] = n == 0 ? 1.0 : 2.0 * cos((double)n * th);
+            A[e] = n == 0 ? 1.0 : 2.0 * cos((double)n * th);
         } else {
-            int c = i - L;
+            const int n = (e - L * K) / Lc, c = (e - L * K) % Lc;
             double th = ((double)c + 0.5) * kPi / (double)Lc;
-            C[(size_t)c * K + n] = n == 0 ? 1.0 : 2.0 * cos((double)n * th);
+            Ct[(size_t)n * Lc + c] = n == 0 ? 1.0 : 2.0 * cos((double)n * th);
         }
     }
-}
-
-struct DesignShared {
-    double G[kMaxK * kMaxK];
-    double br[kMaxK], bi[kMaxK];
-    double hr[kMaxK], hi[kMaxK];
-    double red[kDesignThreads];
-    int fail;
-};
-
-// Normal equations (A^T W A + lambda I) h = A^T W D, Cholesky, two real RHS.
-__device__ void wls_solve(const double* __restrict__ A, const double* w,
-                          const double* Dr, const double* Di, int L, int K,
-                          double lambda, DesignShared& sh)
-{
-#pragma clang fp contract(off)
-    const int npair = K * (K + 1) / 2;
-    for (int task = threadIdx.x; task < npair + K; task += blockDim.x) {
-        if (task < npair) {
-            // lower-triangle pair (p, q), q <= p
-            int p = 0;
-            while ((p + 1) * (p + 2) / 2 <= task) ++p;
-            int q = task - p * (p + 1) / 2;
-            // Loads of 8 grid points are issued ahead of their (sequential,
-            // grid-ordered) accumulation, which keeps the oracle's order.
-            double s = 0.0;
-            int i = 0;
-            for (; i + 8 <= L; i += 8) {
-                double wv[8], ap[8], aq[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    wv[u] = w[i + u];
-                    ap[u] = A[(size_t)(i + u) * K + p];
-                    aq[u] = A[(size_t)(i + u) * K + q];
-                }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) s += wv[u] * ap[u] * aq[u];
-            }
-            for (; i < L; ++i) {
-                const double* a = A + (size_t)i * K;
-                s += w[i] * a[p] * a[q];
-            }
-            if (p == q) s += lambda;
-            sh.G[p * K + q] = s;
-        } else {
-            int p = task - npair;
-            double sr = 0.0, si = 0.0;
-            int i = 0;
-            for (; i + 8 <= L; i += 8) {
-                double wv[8], ap[8], dr[8], di[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    wv[u] = w[i + u];
-                    ap[u] = A[(size_t)(i + u) * K + p];
-                    dr[u] = Dr[i + u];
-                    di[u] = Di[i + u];
-                }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const double wa = wv[u] * ap[u];
-                    sr += wa * dr[u];
-                    si += wa * di[u];
-                }
-            }
-            for (; i < L; ++i) {
-                double wa = w[i] * A[(size_t)i * K + p];
-                sr += wa * Dr[i];
-                si += wa * Di[i];
-            }
-            sh.br[p] = sr;
-            sh.bi[p] = si;
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double* G = sh.G;
-        for (int p = 0; p < K; ++p) {
-            for (int q = 0; q <= p; ++q) {
-                double s = G[p * K + q];
-                for (int m = 0; m < q; ++m) s -= G[p * K + m] * G[q * K + m];
-                if (p == q) {
-                    if (!(s > 0.0)) { sh.fail = 1; s = 1.0; }
-                    G[p * K + p] = sqrt(s);
-                } else {
-                    G[p * K + q] = s / G[q * K + q];
-                }
-            }
-        }
-        for (int p = 0; p < K; ++p) {
-            double sr = sh.br[p], si = sh.bi[p];
-            for (int m = 0; m < p; ++m) { sr -= G[p * K + m] * sh.br[m]; si -= G[p * K + m] * sh.bi[m]; }
-            sh.br[p] = sr / G[p * K + p];
-            sh.bi[p] = si / G[p * K + p];
-        }
-        for (int p = K - 1; p >= 0; --p) {
-            double sr = sh.br[p], si = sh.bi[p];
-            for (int m = p + 1; m < K; ++m) { sr -= G[m * K + p] * sh.br[m]; si -= G[m * K + p] * sh.bi[m]; }
-            sh.br[p] = sr / G[p * K + p];
-            sh.bi[p] = si / G[p * K + p];
-        }
-        for (int p = 0; p < K; ++p) { sh.hr[p] = sh.br[p]; sh.hi[p] = sh.bi[p]; }
-    }
-    __syncthreads();
-}
-
-__device__ double block_max(double v, DesignShared& sh)
-{
-    sh.red[threadIdx.x] = v;
-    __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s) sh.red[threadIdx.x] = fmax(sh.red[threadIdx.x], sh.red[threadIdx.x + s]);
-        __syncthreads();
-    }
-    double r = sh.red[0];
-    __syncthreads();
-    return r;
 }
 
 struct DesignParams {
@@ -190,88 +78,6 @@ DesignParams design_params(const mig_table_desc* d)
     return P;
 }
 
-__global__ void __launch_bounds__(kDesignThreads)
-k_design(DesignParams P, const double* __restrict__ A, const double* __restrict__ C,
-         mig_c128* tab64, mig_c64* tab32, double* maxgain, double* passerr,
-         int* status)
-{
-#pragma clang fp contract(off)
-    extern __shared__ double dyn[];
-    __shared__ DesignShared sh;
-    const int j = blockIdx.x, K = P.K, L = P.L, Lc = P.Lc;
-    double* w = dyn;
-    double* Dr = dyn + L;
-    double* Di = dyn + 2 * L;
-
-    const double kappa = (P.kmin + (double)j * P.dk) * P.dx;
-    const double edge = kappa * P.edge_sin;
-    if (threadIdx.x == 0) sh.fail = 0;
-    for (int i = threadIdx.x; i < L; i += blockDim.x) {
-        double th = ((double)i + 0.5) * kPi / (double)L;
-        if (th <= kappa) {
-            double ph = P.zeta * sqrt(kappa * kappa - th * th);
-            double sn, cs;
-            sincos(ph, &sn, &cs);
-            Dr[i] = cs;
-            Di[i] = sn;
-        } else {
-            Dr[i] = exp(-P.zeta * sqrt(th * th - kappa * kappa));
-            Di[i] = 0.0;
-        }
-        w[i] = th <= edge ? P.w_pass : (th <= kappa ? P.w_trans : P.w_evan);
-    }
-    __syncthreads();
-
-    wls_solve(A, w, Dr, Di, L, K, P.lambda, sh);
-    for (int it = 0; it < P.nreweight; ++it) {
-        for (int i = threadIdx.x; i < L; i += blockDim.x) {
-            double Hr = 0.0, Hi = 0.0;
-            const double* a = A + (size_t)i * K;
-            for (int n = 0; n < K; ++n) { Hr += a[n] * sh.hr[n]; Hi += a[n] * sh.hi[n]; }
-            double excess = hypot(Hr, Hi) - 1.0;
-            if (excess > 0.0) w[i] = w[i] * (1.0 + P.beta * excess / P.tau);
-        }
-        __syncthreads();
-        wls_solve(A, w, Dr, Di, L, K, P.lambda, sh);
-    }
-
-    // Stability scale: |H|max <= max_grid |H| / cos(M pi / (2 Lc)).
-    double g = 0.0;
-    for (int c = threadIdx.x; c < Lc; c += blockDim.x) {
-        const double* cc = C + (size_t)c * K;
-        double Hr = sh.hr[0], Hi = sh.hi[0];
-        for (int n = 1; n < K; ++n) { Hr += cc[n] * sh.hr[n]; Hi += cc[n] * sh.hi[n]; }
-        g = fmax(g, hypot(Hr, Hi));
-    }
-    g = block_max(g, sh);
-    double s = 1.0;
-    double lim = (1.0 - P.margin) * cos((double)(K - 1) * kPi / (2.0 * (double)Lc));
-    if (g > lim) s = lim / g;
-
-    double perr = 0.0;
-    for (int i = threadIdx.x; i < L; i += blockDim.x) {
-        double th = ((double)i + 0.5) * kPi / (double)L;
-        if (!(th <= edge)) continue;
-        const double* a = A + (size_t)i * K;
-        double Hr = 0.0, Hi = 0.0;
-        for (int n = 0; n < K; ++n) { Hr += a[n] * (s * sh.hr[n]); Hi += a[n] * (s * sh.hi[n]); }
-        perr = fmax(perr, hypot(Hr - Dr[i], Hi - Di[i]));
-    }
-    perr = block_max(perr, sh);
-
-    for (int n = threadIdx.x; n < K; n += blockDim.x) {
-        double hr = s * sh.hr[n], hi = s * sh.hi[n];
-        tab64[(size_t)j * K + n] = mig_c128{hr, hi};
-        if (tab32) tab32[(size_t)j * K + n] = mig_c64{(float)hr, (float)hi};
-    }
-    if (threadIdx.x == 0) {
-        double mg = s * g;
-        if (maxgain) maxgain[j] = mg;
-        if (passerr) passerr[j] = perr;
-        status[j] = sh.fail ? 2 : (mg <= 1.0 ? 0 : 1);
-    }
-}
-
 // ---- 2-D circularly symmetric extrapolators (3-D extension, Sec. II) ----
 //
 // Unique coefficient u = a (a + 1) / 2 + b, a >= b >= 0, stands for the taps
@@ -299,7 +105,7 @@ __global__ void k_design2d_basis(int L, int Lc, int M, double* A, double* CS)
          e += (size_t)gridDim.x * blockDim.x) {
         if (e < nA) {
             const int i = (int)(e / L), q = (int)(e % L);
-            double cx[kMaxK], cy[kMaxK];
+            double cx[kMaxM2 + 1], cy[kMaxM2 + 1];
             const double tx = ((double)i + 0.5) * kPi / (double)L;
             const double ty = ((double)q + 0.5) * kPi / (double)L;
             for (int n = 0; n <= M; ++n) { cx[n] = cos((double)n * tx); cy[n] = cos((double)n * ty); }
@@ -313,97 +119,627 @@ __global__ void k_design2d_basis(int L, int Lc, int M, double* A, double* CS)
     }
 }
 
-__global__ void __launch_bounds__(kDesignThreads)
-k_design2d(DesignParams P, const double* __restrict__ A, const double* __restrict__ CS,
-           mig_c128* tab64, mig_c64* tab32, double* maxgain, double* passerr, int* status)
+typedef double v2f64 __attribute__((ext_vector_type(2)));
+
+// Stored weights and targets per entry: the grid, or in two dimensions its points
+// with q <= i (basis row, target and weight of (i, q) and (q, i) are equal).
+__host__ __device__ constexpr int design_points(int L, bool two_d) { return two_d ? L * (L + 1) / 2 : L; }
+
+// Waves of a workgroup: as many as its tiles of 2 x 2 sums need (K (K+2) / 8
+// of the normal matrix and K / 2 per entry of the right-hand sides: 63 at K = 18 and
+// two entries, 102 at 24, 168 at 32).
+__host__ __device__ constexpr int design_waves(int KT) { return KT <= 18 ? 1 : (KT <= 24 ? 2 : 3); }
+
+constexpr int kDesignChunk = 64;  // grid points per chunk of the basis
+
+// A grid point's row in LDS, in doubles: KT basis values (an even count), the targets
+// of the workgroup's EB entries, their weights.  Pairs are 16-byte aligned (LDS returns
+// 16-byte reads at twice the rate of 8-byte ones) and the stride is an odd multiple of
+// two pairs (no bank conflicts where each lane reads another row).
+__host__ __device__ constexpr int design_target_col(int KT) { return (KT + 1) & ~1; }
+__host__ __device__ constexpr int design_weight_col(int KT, int eb) { return design_target_col(KT) + 2 * eb; }
+__host__ __device__ constexpr int design_stride(int KT, int eb)
+{
+    const int n = design_weight_col(KT, eb) + eb;
+    return n <= 2 ? 2 : (n + 1) / 4 * 4 + 2;
+}
+
+// LDS, in doubles: weights (and, in two dimensions, targets) of every entry; the
+// solver's exchange rows and solution; the chunk's rows or, between two passes over
+// the grid, the systems.
+struct DesignLds {
+    int w, d, x, h, a, g, total;
+};
+
+__host__ __device__ inline DesignLds design_lds(int L, int KT, int eb, bool two_d)
+{
+    DesignLds o;
+    const int np = design_points(L, two_d);
+    int at = 0;
+    o.w = at;
+    at += (np * eb + 1) & ~1;
+    o.d = at;
+    at += two_d ? 2 * np * eb : 0;
+    o.x = at;
+    at += eb * 4 * (KT + 2);
+    o.h = at;
+    at += eb * 2 * KT;
+    o.a = o.g = at;
+    const int rows = kDesignChunk * design_stride(KT, eb) + 2, sys = eb * (KT + 2) * (KT | 1);
+    o.total = at + (rows > sys ? rows : sys);
+    return o;
+}
+
+__device__ __forceinline__ void wave_lds_fence()
+{
+    // LDS keeps one wave's accesses in order: only the compiler has to
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// Cholesky of the lower triangle G (rows of stride KT | 1) with the right-hand sides
+// as rows KT and KT + 1, then the back substitution, by the lanes r = 0 .. KT+1 of one
+// wave or half of one: lane r keeps row r in registers (rows K .. KT-1 are the
+// identity's) and per column the lanes exchange their column values and diagonals
+// through x once.  Every element sees its subtractions in the order of a sequential
+// Cholesky and substitution.
+template <int KT>
+__device__ __forceinline__ void design_solve(const double* G, v2f64* x, v2f64* h, int K, int r, int* fail)
 {
 #pragma clang fp contract(off)
-    extern __shared__ double dyn[];
-    __shared__ DesignShared sh;
-    const int j = blockIdx.x, NU = P.K, L = P.L, Lc = P.Lc, LL = L * L;
-    const int M = P.M;
-    double* w = dyn;
-    double* Dr = dyn + LL;
-    double* Di = dyn + 2 * LL;
-
-    const double kappa = (P.kmin + (double)j * P.dk) * P.dx;
-    const double k2 = kappa * kappa;
-    const double edge = kappa * P.edge_sin;
-    if (threadIdx.x == 0) sh.fail = 0;
-    for (int e = threadIdx.x; e < LL; e += blockDim.x) {
-        const double tx = ((double)(e / L) + 0.5) * kPi / (double)L;
-        const double ty = ((double)(e % L) + 0.5) * kPi / (double)L;
-        const double r2 = tx * tx + ty * ty;
-        const double r = sqrt(r2);
-        if (r2 <= k2) {
-            double sn, cs;
-            sincos(P.zeta * sqrt(k2 - r2), &sn, &cs);
-            Dr[e] = cs;
-            Di[e] = sn;
-        } else {
-            Dr[e] = exp(-P.zeta * sqrt(r2 - k2));
-            Di[e] = 0.0;
-        }
-        w[e] = r <= edge ? P.w_pass : (r <= kappa ? P.w_trans : P.w_evan);
+    // a value the compiler cannot see through: what follows from it (a mask per column)
+    // is formed here each time, not kept in registers over the passes
+    asm volatile("" : "+v"(r));
+    constexpr int LD = KT | 1;
+    const bool rhs = r == KT || r == KT + 1, in = r < K;
+    const double* const row = G + (rhs || in ? r : 0) * LD;
+    // columns are exchanged as pairs; scheduling barriers keep the registers of the
+    // values in flight to a few pairs
+    double* const col = reinterpret_cast<double*>(x);
+    double* const dg = col + KT + 2 + (KT & 1);
+    double g[KT];
+#pragma unroll
+    for (int q = 0; q < KT; ++q) {
+        const double v = row[q];
+        g[q] = q < K && (rhs || (in && q <= r)) ? v : 0.0;
+        if (q % 8 == 7) __builtin_amdgcn_sched_barrier(0);
     }
-    __syncthreads();
-
-    wls_solve(A, w, Dr, Di, LL, NU, P.lambda, sh);
-    for (int it = 0; it < P.nreweight; ++it) {
-        for (int e = threadIdx.x; e < LL; e += blockDim.x) {
-            double Hr = 0.0, Hi = 0.0;
-            const double* a = A + (size_t)e * NU;
-            for (int u = 0; u < NU; ++u) { Hr += a[u] * sh.hr[u]; Hi += a[u] * sh.hi[u]; }
-            const double excess = hypot(Hr, Hi) - 1.0;
-            if (excess > 0.0) w[e] = w[e] * (1.0 + P.beta * excess / P.tau);
+    double diag = in ? row[in ? r : 0] : 1.0;
+    double pivot = G[0];
+    bool bad = false;
+#pragma unroll
+    for (int m = 0; m < KT; ++m) {
+        if (!(pivot > 0.0)) {
+            bad = true;
+            pivot = 1.0;
         }
+        const double d = sqrt(pivot);
+        const double l = r == m ? d : g[m] / d;
+        g[m] = l;
+        if (r < KT + 2) {
+            col[r] = l;
+            dg[r] = diag;
+        }
+        wave_lds_fence();
+        if (m + 1 < KT) {
+            const double n = col[m + 1 < KT ? m + 1 : m];
+            pivot = dg[m + 1 < KT ? m + 1 : m] - n * n;
+        }
+#pragma unroll
+        for (int q = (m + 1) & ~1; q < KT; q += 2) {
+            const v2f64 c = x[q / 2];  // column values q, q + 1
+            if (q > m) g[q] -= l * c.x;
+            if (q + 1 < KT) g[q + 1 < KT ? q + 1 : q] -= l * c.y;
+            if (q % 8 == 6) __builtin_amdgcn_sched_barrier(0);
+        }
+        diag -= l * l;
+        wave_lds_fence();
+    }
+    if (bad && r == 0) *fail = 1;
+    // x: the transformed right-hand sides; then, per unknown m, the products of the
+    // lanes q > m that are subtracted from it
+    v2f64* const p = x + KT + 2;
+    if (rhs)
+#pragma unroll
+        for (int q = 0; q < KT; ++q) col[2 * q + r - KT] = g[q];
+    wave_lds_fence();
+    double xr = 0.0, xi = 0.0;
+#pragma unroll
+    for (int m = KT - 1; m >= 0; --m) {
+        if (r < KT) p[r] = v2f64{g[m] * xr, g[m] * xi};
+        wave_lds_fence();
+        v2f64 s = x[m];
+#pragma unroll
+        for (int q = m + 1; q < KT; ++q) {
+            const v2f64 v = p[q];
+            s.x -= v.x;
+            s.y -= v.y;
+            if ((q - m) % 8 == 0) __builtin_amdgcn_sched_barrier(0);
+        }
+        if (r == m) {
+            xr = s.x / g[m];
+            xi = s.y / g[m];
+            h[m] = v2f64{xr, xi};
+        }
+        wave_lds_fence();
+    }
+}
+
+// Phase shift over dz at kz^2 = q (in units of dx), or the decay past the cutoff.  A
+// function of its own keeps its constants out of the caller's registers.
+__device__ __noinline__ v2f64 design_target(double zeta, double q, bool propagating)
+{
+#pragma clang fp contract(off)
+    if (propagating) {
+        double sn, cs;
+        sincos(zeta * sqrt(q), &sn, &cs);
+        return v2f64{cs, sn};
+    }
+    return v2f64{exp(-zeta * sqrt(-q)), 0.0};
+}
+
+// Basis rows and targets of the chunk at c0.
+template <int NV, int NE, int T, bool TWO_D>
+__device__ __forceinline__ void design_fetch(v2f64 (&pre)[NV], v2f64 (&dpre)[NE], const double* A,
+                                             const v2f64* Dg, int c0, int LL, int K, int t, int ip)
+{
+    const int last = ((LL * K + 1) & ~1) - 2;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const int at = c0 * K + 2 * (v * T + t);
+        pre[v] = *reinterpret_cast<const v2f64*>(A + (at < last ? at : last));
+    }
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+        dpre[e] = TWO_D ? v2f64{0.0, 0.0} : Dg[e * LL + (c0 + ip < LL ? c0 + ip : LL - 1)];
+}
+
+// Bound by instruction issue (one wave per SIMD: about 6 cycles per FP64 operation).
+// 35 taps, 2048 entries: 16.0 -> 2.82 ms per table; 11 x 11 taps, 1024 entries: 28.5 ->
+// 5.7 ms (before: one workgroup per entry, a thread per sum reading the basis from L2,
+// the solves on one thread).  Of a pass of two 35-tap entries the sums take 147 k of
+// 214 k cycles, the responses 29 k, the solves 21 k, the chunks' copies 13 k.
+//
+// No branch that part of a wave takes holds the sums (threads past the tiles repeat
+// the first one's), and the loops keep within 256 registers: with a mask around them
+// and registers moved to the accumulation file inside, idle lanes came out with other
+// lanes' addresses.
+template <int EB, int KT, bool TWO_D>
+__global__ void __launch_bounds__(64 * design_waves(KT))
+k_design(DesignParams P, const double* __restrict__ A, const double* __restrict__ C, v2f64* D,
+         mig_c128* tab64, mig_c64* tab32, double* maxgain, double* passerr, int* status)
+{
+#pragma clang fp contract(off)
+    extern __shared__ v2f64 dyn2[];
+    double* const dyn = reinterpret_cast<double*>(dyn2);
+    constexpr int W = design_waves(KT), T = 64 * W, CH = kDesignChunk;
+    constexpr int RS = design_stride(KT, EB), RP = RS / 2, LD = KT | 1;
+    constexpr int DC = design_target_col(KT), WC = design_weight_col(KT, EB);
+    __shared__ double s_red[EB][W];
+    __shared__ int s_fail[EB];
+    const int K = P.K, L = P.L, t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int LL = TWO_D ? L * L : L, np = design_points(L, TWO_D);
+    const DesignLds o = design_lds(L, KT, EB, TWO_D);
+    double* const w = dyn + o.w;
+    double* const rows = dyn + o.a;
+    const v2f64* const rows2 = dyn2 + o.a / 2;
+    v2f64* const hs = dyn2 + o.h / 2;
+
+    // this thread's share of a chunk: point ip of entries e0 .. e0 + NE - 1 (a wave per
+    // entry where there are enough)
+    constexpr int NE = W >= EB ? 1 : EB;
+    const int ip = t & 63, e0 = NE == 1 && wave < EB ? wave : 0;
+    const bool mine = NE > 1 || wave < EB;
+    // this thread's tile: coefficients 2 bp, 2 bp + 1 against 2 bq, 2 bq + 1, or
+    // against the right-hand sides of entry aug
+    const int nb = (K + 1) / 2, ntri = nb * (nb + 1) / 2;
+    const bool tile = t < ntri + nb * EB;
+    int bp = 0, bq = 0, aug = -1;
+    if (t < ntri) {
+        while ((bp + 1) * (bp + 2) / 2 <= t) ++bp;
+        bq = t - bp * (bp + 1) / 2;
+    } else if (tile) {
+        aug = (t - ntri) / nb;
+        bp = (t - ntri) % nb;
+    }
+    const v2f64* const pa = rows2 + bp;
+    const v2f64* const qa = rows2 + (aug < 0 ? bq : DC / 2 + aug);
+    const double* const wa = rows + WC;
+    // LDS places of the basis values this thread copies per chunk (values past the
+    // chunk's rows go to the place after them)
+    constexpr int NV = (CH * KT / 2 + T - 1) / T;
+    int to[NV][2];
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int at = 2 * (v * T + t) + u, row = at / K;
+            to[v][u] = row < CH ? row * RS + at - row * K : CH * RS;
+        }
+
+    for (int gi = blockIdx.x; gi * EB < P.nk; gi += gridDim.x) {
+        // the entries of this workgroup (past the table's end: the last one again)
+        const int j0 = gi * EB;
+        v2f64* const Dg = TWO_D ? dyn2 + o.d / 2 : D + (size_t)blockIdx.x * EB * L;
         __syncthreads();
-        wls_solve(A, w, Dr, Di, LL, NU, P.lambda, sh);
-    }
-
-    // Stability scale: the per-axis Bernstein bound applied twice,
-    // |H|max <= max_grid |H| / cos(M pi / (2 Lc))^2.
-    double g = 0.0;
-    for (int e = threadIdx.x; e < Lc * Lc; e += blockDim.x) {
-        const double* cx = CS + (size_t)(e / Lc) * (M + 1);
-        const double* cy = CS + (size_t)(e % Lc) * (M + 1);
-        double Hr = 0.0, Hi = 0.0;
-        for (int a = 0, u = 0; a <= M; ++a)
-            for (int b = 0; b <= a; ++b, ++u) {
-                const double f = orbit_basis(a, b, cx, cy);
-                Hr += f * sh.hr[u];
-                Hi += f * sh.hi[u];
+        for (int v = t; v < np * EB; v += T) {
+            const int e = v / np, x = v - e * np;
+            const int j = j0 + e < P.nk ? j0 + e : P.nk - 1;
+            const double kappa = (P.kmin + (double)j * P.dk) * P.dx;
+            const double edge = kappa * P.edge_sin;
+            double r, r2;
+            if (TWO_D) {
+                int i = (int)((sqrt(8.0 * (double)x + 1.0) - 1.0) * 0.5);
+                while (i * (i + 1) / 2 > x) --i;
+                while ((i + 1) * (i + 2) / 2 <= x) ++i;
+                const double tx = ((double)i + 0.5) * kPi / (double)L;
+                const double ty = ((double)(x - i * (i + 1) / 2) + 0.5) * kPi / (double)L;
+                r2 = tx * tx + ty * ty;
+                r = sqrt(r2);
+            } else {
+                r = ((double)x + 0.5) * kPi / (double)L;
+                r2 = r * r;
             }
-        g = fmax(g, hypot(Hr, Hi));
-    }
-    g = block_max(g, sh);
-    const double c = cos((double)M * kPi / (2.0 * (double)Lc));
-    const double lim = (1.0 - P.margin) * c * c;
-    const double s = g > lim ? lim / g : 1.0;
+            const double k2 = kappa * kappa;
+            Dg[v] = design_target(P.zeta, k2 - r2, TWO_D ? r2 <= k2 : r <= kappa);
+            w[v] = r <= edge ? P.w_pass : (r <= kappa ? P.w_trans : P.w_evan);
+        }
+        for (int v = t; v < EB * KT; v += T) hs[v] = v2f64{0.0, 0.0};  // coefficients past K
+        if (t < EB) s_fail[t] = 0;
+        __syncthreads();
 
-    double perr = 0.0;
-    for (int e = threadIdx.x; e < LL; e += blockDim.x) {
-        const double tx = ((double)(e / L) + 0.5) * kPi / (double)L;
-        const double ty = ((double)(e % L) + 0.5) * kPi / (double)L;
-        if (!(sqrt(tx * tx + ty * ty) <= edge)) continue;
-        const double* a = A + (size_t)e * NU;
-        double Hr = 0.0, Hi = 0.0;
-        for (int u = 0; u < NU; ++u) { Hr += a[u] * (s * sh.hr[u]); Hi += a[u] * (s * sh.hi[u]); }
-        perr = fmax(perr, hypot(Hr - Dr[e], Hi - Di[e]));
-    }
-    perr = block_max(perr, sh);
+        for (int it = 0; it <= P.nreweight; ++it) {
+            double acc[EB][2][2];
+#pragma unroll
+            for (int e = 0; e < EB; ++e)
+                acc[e][0][0] = acc[e][0][1] = acc[e][1][0] = acc[e][1][1] = 0.0;
+            // basis columns K .. KT-1 are zeros (the systems had their place)
+            for (int v = t; v < CH * (KT - K); v += T) rows[v / (KT - K) * RS + K + v % (KT - K)] = 0.0;
+            // The chunk's basis rows (contiguous) and targets are loaded one chunk
+            // ahead, without branches (a load that may not have been issued would be
+            // waited for at once): addresses are clamped into the grid, whose last
+            // pair may reach into the workspace's padding, and rows past the chunk's
+            // are copied but not read.
+            v2f64 pre[NV], dpre[NE];
+            design_fetch<NV, NE, T, TWO_D>(pre, dpre, A, Dg + e0 * LL, 0, LL, K, t, ip);
+            for (int c0 = 0; c0 < LL; c0 += CH) {
+                const int n = LL - c0 < CH ? LL - c0 : CH;
+                __syncthreads();  // the previous chunk has been summed
+                v2f64 dn[NE];
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    rows[to[v][0]] = pre[v].x;
+                    rows[to[v][1]] = pre[v].y;
+                }
+#pragma unroll
+                for (int e = 0; e < NE; ++e) dn[e] = dpre[e];
+                design_fetch<NV, NE, T, TWO_D>(pre, dpre, A, Dg + e0 * LL, c0 + CH < LL ? c0 + CH : 0, LL, K, t, ip);
+                __syncthreads();
+                int x = c0 + ip < LL ? c0 + ip : LL - 1;
+                asm volatile("" : "+v"(x));
+                bool mirrored = false;
+                if (TWO_D) {
+                    const int i = x / L, q = x - i * L;
+                    mirrored = i > q;  // its mirror image came first and updates the weight
+                    x = mirrored ? i * (i + 1) / 2 + q : q * (q + 1) / 2 + i;
+                }
+                double wv[NE];
+#pragma unroll
+                for (int e = 0; e < NE; ++e) wv[e] = w[(e0 + e) * np + x];
+                if (it > 0 && mine) {
+                    // response of the last fit, and the weights where it exceeds one
+                    const v2f64* const a2 = rows2 + ip * RP;
+                    double Hr[NE] = {}, Hi[NE] = {};
+#pragma unroll
+                    for (int q = 0; q < KT; q += 2) {  // coefficients past K are zero
+                        const v2f64 a = a2[q / 2];
+#pragma unroll
+                        for (int e = 0; e < NE; ++e) {
+                            const v2f64 h0 = hs[(e0 + e) * KT + q];
+                            Hr[e] += a.x * h0.x;
+                            Hi[e] += a.x * h0.y;
+                            if (q + 1 < KT) {
+                                const v2f64 h1 = hs[(e0 + e) * KT + (q + 1 < KT ? q + 1 : q)];
+                                Hr[e] += a.y * h1.x;
+                                Hi[e] += a.y * h1.y;
+                            }
+                        }
+                        if (q % 6 == 4) __builtin_amdgcn_sched_barrier(0);
+                    }
+#pragma unroll
+                    for (int e = 0; e < NE; ++e)
+                        // clearly below one: no excess (hypot errs by an ulp)
+                        if (ip < n && !mirrored && !(Hr[e] * Hr[e] + Hi[e] * Hi[e] < 1.0 - 1e-12)) {
+                            const double excess = hypot(Hr[e], Hi[e]) - 1.0;
+                            if (excess > 0.0) {
+                                wv[e] = wv[e] * (1.0 + P.beta * excess / P.tau);
+                                w[(e0 + e) * np + x] = wv[e];
+                            }
+                        }
+                }
+                if (TWO_D) {
+                    __syncthreads();  // both images of a point may lie in this chunk
+#pragma unroll
+                    for (int e = 0; e < NE; ++e) {
+                        wv[e] = w[(e0 + e) * np + x];
+                        dn[e] = Dg[(e0 + e) * np + x];
+                    }
+                }
+                if (mine)
+#pragma unroll
+                    for (int e = 0; e < NE; ++e) {
+                        rows[ip * RS + WC + e0 + e] = wv[e];
+                        *reinterpret_cast<v2f64*>(rows + ip * RS + DC + 2 * (e0 + e)) = dn[e];
+                    }
+                __syncthreads();
+                // Few waves share a SIMD here, so the order is explicit: U grid points'
+                // operands are read while the U before them are summed, and each point's
+                // products stand apart from their sums.
+                constexpr int U = 4;
+                struct Ops {
+                    v2f64 p, q;
+                    double w[EB];
+                };
+                auto read1 = [&](Ops& v, int i) {
+                    v.p = pa[i * RP];
+                    v.q = qa[i * RP];
+                    if constexpr (EB == 2) {
+                        const v2f64 w2 = *reinterpret_cast<const v2f64*>(wa + i * RS);
+                        v.w[0] = w2.x;
+                        v.w[EB - 1] = w2.y;
+                    } else {
+                        v.w[0] = wa[i * RS];
+                    }
+                };
+                auto read = [&](Ops (&v)[U], int i) {
+#pragma unroll
+                    for (int u = 0; u < U; ++u) read1(v[u], i + u);
+                };
+                auto add = [&](const Ops& v) {
+                    double w0[EB], w1[EB], m[EB][2][2];
+#pragma unroll
+                    for (int e = 0; e < EB; ++e) {
+                        w0[e] = v.w[e] * v.p.x;
+                        w1[e] = v.w[e] * v.p.y;
+                    }
+#pragma unroll
+                    for (int e = 0; e < EB; ++e) {
+                        m[e][0][0] = w0[e] * v.q.x;
+                        m[e][0][1] = w0[e] * v.q.y;
+                        m[e][1][0] = w1[e] * v.q.x;
+                        m[e][1][1] = w1[e] * v.q.y;
+                    }
+#pragma unroll
+                    for (int e = 0; e < EB; ++e) {
+                        acc[e][0][0] += m[e][0][0];
+                        acc[e][0][1] += m[e][0][1];
+                        acc[e][1][0] += m[e][1][0];
+                        acc[e][1][1] += m[e][1][1];
+                    }
+                };
+                const int full = n / (2 * U) * (2 * U);
+                Ops va[U], vb[U];
+                if (full > 0) read(va, 0);
+                for (int i = 0; i < full; i += 2 * U) {
+                    read(vb, i + U);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int u = 0; u < U; ++u) add(va[u]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    read(va, i + 2 * U < full ? i + 2 * U : 0);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int u = 0; u < U; ++u) add(vb[u]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                for (int i = full; i < n; ++i) {
+                    Ops v;
+                    read1(v, i);
+                    add(v);
+                }
+            }
+            // the systems take the rows' place
+            __syncthreads();
+            if (tile)
+#pragma unroll
+                for (int e = 0; e < EB; ++e) {
+                    double* const G = dyn + o.g + e * (KT + 2) * LD;
+#pragma unroll
+                    for (int u = 0; u < 2; ++u)
+#pragma unroll
+                        for (int v = 0; v < 2; ++v) {
+                            const int p = 2 * bp + u, q = 2 * bq + v;
+                            double s = acc[e][u][v];
+                            if (aug >= 0) {
+                                if (aug == e && p < K) G[(KT + v) * LD + p] = s;
+                            } else if (p < K && q <= p) {
+                                if (p == q) s += P.lambda;
+                                G[p * LD + q] = s;
+                            }
+                        }
+                }
+            __syncthreads();
+            // a wave per entry, or half a wave (KT <= 18: 32 lanes hold the KT + 2 rows)
+            {
+                constexpr bool half = NE > 1;
+                int se = half ? t >> 5 : wave;
+                const int sr = half ? t & 31 : t & 63;
+                asm volatile("" : "+v"(se));
+                if (half || wave < EB)
+                    design_solve<KT>(dyn + o.g + se * (KT + 2) * LD, dyn2 + o.x / 2 + se * 2 * (KT + 2),
+                                     hs + se * KT, K, sr, &s_fail[se]);
+            }
+            __syncthreads();
+        }
 
-    for (int u = threadIdx.x; u < NU; u += blockDim.x) {
-        const double hr = s * sh.hr[u], hi = s * sh.hi[u];
-        tab64[(size_t)j * NU + u] = mig_c128{hr, hi};
-        if (tab32) tab32[(size_t)j * NU + u] = mig_c64{(float)hr, (float)hi};
+        // Stability scale: |H|max <= max_grid |H| / cos(M pi / (2 Lc)) (in two dimensions
+        // the bound applies along each axis, hence squared).
+        double g[EB], g2[EB];  // g2 screens points whose |H| cannot be the largest
+#pragma unroll
+        for (int e = 0; e < EB; ++e) g[e] = g2[e] = 0.0;
+        auto raise = [&](int e, double Hr, double Hi) {
+            const double s2 = Hr * Hr + Hi * Hi;
+            if (!(s2 < g2[e])) {
+                g[e] = fmax(g[e], hypot(Hr, Hi));
+                g2[e] = s2 * (1.0 - 1e-12);
+            }
+        };
+        if constexpr (TWO_D) {
+            // |H| is symmetric: points with q <= i
+            const int Lc = P.Lc, M = P.M;
+            for (int x = t; x < Lc * Lc; x += T) {
+                const int i = x / Lc, q = x - i * Lc;
+                if (q > i) continue;
+                double cx[kMaxM2 + 1], cy[kMaxM2 + 1];
+#pragma unroll
+                for (int a = 0; a <= kMaxM2; ++a) {
+                    cx[a] = C[(size_t)i * (M + 1) + (a <= M ? a : 0)];
+                    cy[a] = C[(size_t)q * (M + 1) + (a <= M ? a : 0)];
+                }
+                double Hr[EB] = {}, Hi[EB] = {};
+#pragma unroll
+                for (int a = 0; a <= kMaxM2; ++a)
+#pragma unroll
+                    for (int b = 0; b <= a; ++b) {
+                        const int u = a * (a + 1) / 2 + b;
+                        if (u < KT && a <= M) {
+                            const double f = orbit_basis(a, b, cx, cy);
+#pragma unroll
+                            for (int e = 0; e < EB; ++e) {
+                                const v2f64 hv = hs[e * KT + (u < KT ? u : 0)];
+                                Hr[e] += f * hv.x;
+                                Hi[e] += f * hv.y;
+                            }
+                        }
+                    }
+#pragma unroll
+                for (int e = 0; e < EB; ++e) raise(e, Hr[e], Hi[e]);
+            }
+        } else {
+            for (int c = t; c < P.Lc; c += T) {
+                double cc[KT];
+#pragma unroll
+                for (int q = 1; q < KT; ++q) cc[q] = C[(size_t)(q < K ? q : 0) * P.Lc + c];
+#pragma unroll
+                for (int e = 0; e < EB; ++e) {
+                    double Hr = hs[e * KT].x, Hi = hs[e * KT].y;
+#pragma unroll
+                    for (int q = 1; q < KT; ++q) {  // coefficients past K are zero
+                        const v2f64 hv = hs[e * KT + q];
+                        Hr += cc[q] * hv.x;
+                        Hi += cc[q] * hv.y;
+                    }
+                    raise(e, Hr, Hi);
+                }
+            }
+        }
+        auto block_max = [&](double (&v)[EB]) {
+#pragma unroll
+            for (int e = 0; e < EB; ++e) {
+#pragma unroll
+                for (int off = 32; off >= 1; off >>= 1) v[e] = fmax(v[e], __shfl_xor(v[e], off, 64));
+                if ((t & 63) == 0) s_red[e][t >> 6] = v[e];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int e = 0; e < EB; ++e)
+#pragma unroll
+                for (int q = 0; q < W; ++q) v[e] = fmax(v[e], s_red[e][q]);
+            __syncthreads();
+        };
+        block_max(g);
+        const double cb = cos((double)P.M * kPi / (2.0 * (double)P.Lc));
+        const double lim = TWO_D ? (1.0 - P.margin) * cb * cb : (1.0 - P.margin) * cb;
+        double s[EB], perr[EB];
+#pragma unroll
+        for (int e = 0; e < EB; ++e) {
+            s[e] = g[e] > lim ? lim / g[e] : 1.0;
+            perr[e] = 0.0;
+        }
+        for (int x = t; x < LL; x += T) {
+            double r;
+            int at = x;
+            if (TWO_D) {
+                const int i = x / L, q = x - i * L;
+                if (q > i) continue;  // symmetric
+                const double tx = ((double)i + 0.5) * kPi / (double)L;
+                const double ty = ((double)q + 0.5) * kPi / (double)L;
+                r = sqrt(tx * tx + ty * ty);
+                at = i * (i + 1) / 2 + q;
+            } else {
+                r = ((double)x + 0.5) * kPi / (double)L;
+            }
+            const double* a = A + (size_t)x * K;
+#pragma unroll
+            for (int e = 0; e < EB; ++e) {
+                const int j = j0 + e < P.nk ? j0 + e : P.nk - 1;
+                const double kappa = (P.kmin + (double)j * P.dk) * P.dx;
+                if (!(r <= kappa * P.edge_sin)) continue;
+                double Hr = 0.0, Hi = 0.0;
+                for (int q = 0; q < K; ++q) {
+                    Hr += a[q] * (s[e] * hs[e * KT + q].x);
+                    Hi += a[q] * (s[e] * hs[e * KT + q].y);
+                }
+                const v2f64 dv = Dg[e * np + at];
+                perr[e] = fmax(perr[e], hypot(Hr - dv.x, Hi - dv.y));
+            }
+        }
+        block_max(perr);
+#pragma unroll
+        for (int e = 0; e < EB; ++e) {
+            const int j = j0 + e;
+            if (j >= P.nk) continue;
+            for (int q = t; q < K; q += T) {
+                const double hr = s[e] * hs[e * KT + q].x, hi = s[e] * hs[e * KT + q].y;
+                tab64[(size_t)j * K + q] = mig_c128{hr, hi};
+                if (tab32) tab32[(size_t)j * K + q] = mig_c64{(float)hr, (float)hi};
+            }
+            if (t == 0) {
+                const double mg = s[e] * g[e];
+                if (maxgain) maxgain[j] = mg;
+                if (passerr) passerr[j] = perr[e];
+                status[j] = s_fail[e] ? 2 : (mg <= 1.0 ? 0 : 1);
+            }
+        }
     }
-    if (threadIdx.x == 0) {
-        const double mg = s * g;
-        if (maxgain) maxgain[j] = mg;
-        if (passerr) passerr[j] = perr;
-        status[j] = sh.fail ? 2 : (mg <= 1.0 ? 0 : 1);
-    }
+}
+
+template <int EB, int KT, bool TWO_D>
+int launch_design_as(const DesignParams& P, const double* A, const double* C, v2f64* D,
+                     mig_c128* tab64, mig_c64* tab32, double* maxgain, double* passerr, int* status,
+                     hipStream_t s)
+{
+    const size_t lds = (size_t)design_lds(P.L, KT, EB, TWO_D).total * sizeof(double);
+    if (lds > 64000 &&
+        hipFuncSetAttribute(reinterpret_cast<const void*>(&k_design<EB, KT, TWO_D>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        return MIG_E_DEVICE;
+    int blocks = P.nk / EB + (P.nk % EB != 0);
+    if (blocks > kDesignMaxSlots / EB) blocks = kDesignMaxSlots / EB;
+    hipLaunchKernelGGL((k_design<EB, KT, TWO_D>), dim3(blocks), dim3(64 * design_waves(KT)), lds, s,
+                       P, A, C, D, tab64, tab32, maxgain, passerr, status);
+    return hipGetLastError() == hipSuccess ? MIG_OK : MIG_E_DEVICE;
+}
+
+// Loops over coefficients are KT long (zeros past K).  Two entries per workgroup once
+// single ones would put more than one wave on a SIMD: a thread's sums of two entries
+// share their basis reads and fill one wave's issue slots better than two waves do
+// (35 taps, 2048 entries: 2.82 against 3.81 ms; 11 x 11 taps, 1024: 5.7 / 8.3 ms); below
+// that the second entry only lengthens the work of each wave (25 taps, 512 entries: 2.58
+// against 1.85 ms; 9 x 9 taps, 1024: 5.9 / 4.2 ms).
+template <int KT, bool TWO_D>
+int launch_design_kt(const DesignParams& P, const double* A, const double* C, v2f64* D,
+                     mig_c128* tab64, mig_c64* tab32, double* maxgain, double* passerr, int* status,
+                     hipStream_t s)
+{
+    int dev = 0, cus = 256;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        cus = 256;
+    return (long long)P.nk * design_waves(KT) > 4LL * cus
+               ? launch_design_as<2, KT, TWO_D>(P, A, C, D, tab64, tab32, maxgain, passerr, status, s)
+               : launch_design_as<1, KT, TWO_D>(P, A, C, D, tab64, tab32, maxgain, passerr, status, s);
 }
 
 }  // namespace
@@ -424,16 +760,9 @@ int launch_design2d(const mig_table_desc* d, const double* A, const double* CS,
                     int* status, hipStream_t s)
 {
     DesignParams P = design_params(d);
-    P.M = (d->ntaps - 1) / 2;
     P.K = (P.M + 1) * (P.M + 2) / 2;
-    const size_t lds = (size_t)3 * d->ngrid * d->ngrid * sizeof(double);
-    if (lds > 65536 &&
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&k_design2d),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-        return MIG_E_DEVICE;
-    hipLaunchKernelGGL(k_design2d, dim3(d->nk), dim3(kDesignThreads), lds, s, P, A, CS, tab64,
-                       tab32, maxgain, passerr, status);
-    return hipGetLastError() == hipSuccess ? MIG_OK : MIG_E_DEVICE;
+    if (P.K <= 15) return launch_design_kt<15, true>(P, A, CS, nullptr, tab64, tab32, maxgain, passerr, status, s);
+    return launch_design_kt<21, true>(P, A, CS, nullptr, tab64, tab32, maxgain, passerr, status, s);
 }
 
 int launch_design_basis(const mig_table_desc* d, double* A, double* C, hipStream_t s)
@@ -447,16 +776,23 @@ int launch_design_basis(const mig_table_desc* d, double* A, double* C, hipStream
     return hipGetLastError() == hipSuccess ? MIG_OK : MIG_E_DEVICE;
 }
 
-int launch_design(const mig_table_desc* d, const double* A, const double* C,
+size_t design_target_bytes(const mig_table_desc* d)
+{
+    const size_t slots = ((size_t)d->nk + 3) / 4 * 4;
+    return (slots < (size_t)kDesignMaxSlots ? slots : (size_t)kDesignMaxSlots) * d->ngrid * sizeof(double2);
+}
+
+int launch_design(const mig_table_desc* d, const double* A, const double* C, void* targets,
                   mig_c128* tab64, mig_c64* tab32, double* maxgain,
                   double* passerr, int* status, hipStream_t s)
 {
     DesignParams P = design_params(d);
-    P.K = (d->ntaps - 1) / 2 + 1;
-    size_t lds = (size_t)3 * d->ngrid * sizeof(double);
-    hipLaunchKernelGGL(k_design, dim3(d->nk), dim3(kDesignThreads), lds, s, P, A, C,
-                       tab64, tab32, maxgain, passerr, status);
-    return hipGetLastError() == hipSuccess ? MIG_OK : MIG_E_DEVICE;
+    P.K = P.M + 1;
+    v2f64* const D = static_cast<v2f64*>(targets);
+    if (P.K <= 12) return launch_design_kt<12, false>(P, A, C, D, tab64, tab32, maxgain, passerr, status, s);
+    if (P.K <= 18) return launch_design_kt<18, false>(P, A, C, D, tab64, tab32, maxgain, passerr, status, s);
+    if (P.K <= 24) return launch_design_kt<24, false>(P, A, C, D, tab64, tab32, maxgain, passerr, status, s);
+    return launch_design_kt<32, false>(P, A, C, D, tab64, tab32, maxgain, passerr, status, s);
 }
 
 }  // namespace mig
