@@ -185,7 +185,7 @@ inline int row_stride(int nx) { return (nx + 255) / 256 * 256; }
 // 1 = register taps, two outputs per thread, two tap sets (nx <= 1024);
 // 3 = register taps, three outputs per thread, one tap set (nx <= 1536);
 // 2 = register taps, four outputs per thread, one tap set (nx <= 2048);
-// 0 = general kernel, taps read from the table every step.
+// 0 = general kernel (any size), taps in registers or read from the table by wave.
 int extrap_kernel_kind(int nx, int M);
 // Threads one frequency needs in kernel `kind` for nx points.
 int threads_per_omega(int kind, int nx);
@@ -205,7 +205,7 @@ int launch_index(const float* vel, const double* omega, int nx, int nw,
 // steps later; 0 = no flags).
 int launch_slowness(const BatchArgs& a, int max_rows, int max_ldp, int dist, hipStream_t s);
 // Row distance of the change flag a kernel variant reads.
-inline int flag_distance(int kind) { return kind == 1 ? 2 : (kind == 0 ? 0 : 1); }
+inline int flag_distance(int kind) { return kind == 1 ? 2 : 1; }
 // Depth stepping for every workgroup item (+ reducers when sections want rows).
 // `kind` and `threads` (workgroup size) are the same for all items.
 int launch_extrap(const BatchArgs& a, int kind, int threads, hipStream_t s);

@@ -1,0 +1,198 @@
+// Device code shared by the depth-stepping kernels: complex arithmetic of the FIR,
+// partial rows and their publication, the reducer role.
+#pragma once
+
+#include "common.hpp"
+
+namespace mig {
+namespace {
+
+// s_waitcnt vmcnt(0), other counters left alone (GFX9 encoding:
+// vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[5:4] in bits 15:14).
+__device__ __forceinline__ void wait_vmem_all()
+{
+    __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));
+}
+
+__device__ __forceinline__ float2 cmulf(float2 h, float2 u)
+{
+    return make_float2(fmaf(-h.y, u.y, h.x * u.x), fmaf(h.y, u.x, h.x * u.y));
+}
+
+__device__ __forceinline__ float2 cfmaf(float2 h, float2 s, float2 acc)
+{
+    acc.x = fmaf(h.x, s.x, acc.x);
+    acc.x = fmaf(-h.y, s.y, acc.x);
+    acc.y = fmaf(h.x, s.y, acc.y);
+    acc.y = fmaf(h.y, s.x, acc.y);
+    return acc;
+}
+
+__device__ __forceinline__ float2 cadd(float2 a, float2 b)
+{
+    return make_float2(a.x + b.x, a.y + b.y);
+}
+
+// Partial image rows are stored write-through (agent-scope relaxed atomic
+// stores): reducers on other XCDs read them once their block is counted, and
+// nothing of them is left in this XCD's L2 to write back first.
+__device__ __forceinline__ void store_partial2(float* p, float a, float b)
+{
+    const unsigned long long u =
+        (unsigned long long)__float_as_uint(a) | ((unsigned long long)__float_as_uint(b) << 32);
+    __hip_atomic_store(as_global(reinterpret_cast<unsigned long long*>(p)), u, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ SecDev sec_of(const BatchArgs& a, int i)
+{
+    return a.nsec == 1 ? a.one : a.secs[i];
+}
+
+__device__ __forceinline__ ItemDev item_of(const BatchArgs& a, int i)
+{
+    return a.nsec == 1 ? ItemDev{0, i * a.one.G} : a.items[i];
+}
+
+__device__ __forceinline__ TaskDev task_of(const BatchArgs& a, int i)
+{
+    if (a.nsec != 1) return a.tasks[i];
+    const int p = i % a.parts;
+    const int span = ((a.one.nx + a.parts - 1) / a.parts + 1) & ~1;  // even part width
+    const int x0 = p * span;
+    return TaskDev{0, i / a.parts, x0, x0 + span < a.one.nx ? x0 + span : a.one.nx};
+}
+
+// Thread 0 of a frequency workgroup, after a barrier that follows the stores of
+// the partial rows of block c: count the block (and the launch's publishes).  The partial rows are stored
+// write-through (agent-scope atomic stores) and every wave waits for its own
+// stores to complete before that barrier (wait_vmem_all), so when the counter
+// moves the rows are already where other XCDs read them.  No release fence:
+// at agent scope it would write back the whole L2 of the XCD, which the
+// barrier after the next step would make every wave of the workgroup wait for.
+__device__ __forceinline__ void publish_block(const BatchArgs& a, const SecDev& S, int c)
+{
+    if (threadIdx.x == 0) {
+        __hip_atomic_fetch_add(as_global(S.cnt + c), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_add(as_global(a.progress), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+// Block b (steps 32b .. 32b+31) is published at the end of step 32b+33: its
+// last partial row was stored at the start of step 32b+32, the wait for all
+// memory operations at the start of step 32b+33 covers it, and the barrier
+// ending that step means every wave of the workgroup has passed that wait.
+// So no extra wait stands in the loop.  Blocks whose publishing step lies
+// past the last step are published after the loop.
+__device__ __forceinline__ bool publishes_at(int k) { return k >= kPublish + 1 && k % kPublish == 1; }
+__device__ __forceinline__ int published_in_loop(int nsteps)
+{
+    return nsteps - 1 >= kPublish + 1 ? (nsteps - 1 - (kPublish + 1)) / kPublish + 1 : 0;
+}
+
+__device__ __forceinline__ int load_relaxed(int* p)
+{
+    return __hip_atomic_load(as_global(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Thread 0 of a reducer: wait until block T.block of section S is published
+// by all its frequency workgroups.  Returns false when the launch has been
+// abandoned: by this reducer, after kStallTicks (or the caller's limit)
+// without any publish in the launch, or by another reducer before.  The
+// first reducer to give up sets the launch's abandon word and the call's
+// status word; every later wait of the launch returns at once.
+__device__ bool wait_block(const BatchArgs& a, const SecDev& S, int block)
+{
+    int* const abandon = a.progress + 1;
+    const int need = S.nprod + a.extra_wait;
+    int v, last = -1, seen = -1;
+    unsigned long long t0 = wall_clock64();
+    while ((v = load_relaxed(S.cnt + block)) < need) {
+        if (load_relaxed(abandon) != 0) return false;
+        // the stall clock restarts whenever the block's counter or the
+        // launch's publish count moves: a section whose items start late in
+        // a long batch is waited for, a launch that stops is not
+        const int g = load_relaxed(a.progress);
+        const unsigned long long now = wall_clock64();
+        if (v != last || g != seen) {
+            last = v;
+            seen = g;
+            t0 = now;
+        } else if (now - t0 > a.stall_ticks) {
+            __hip_atomic_store(as_global(abandon), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (a.status)
+                __hip_atomic_store(as_global(a.status), kStatusAbandoned, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            return false;
+        }
+        __builtin_amdgcn_s_sleep(kPollSleep);
+    }
+    return true;
+}
+
+// Reducer workgroup q of a.nred: tasks q, q + nred, ... (ordered block-major
+// across sections, i.e. in production order).  One wait and one acquire per
+// task: an acquire invalidates the L2 of the reducer's XCD, which the
+// frequency workgroups there pay for in table refills, so tasks are whole
+// published blocks (split along x only when there are few blocks).
+constexpr int kRedDepth = 32;
+
+__device__ void reduce_role(const BatchArgs& a, int q, int* flag)
+{
+    for (int i = q; i < a.ntasks; i += a.nred) {
+        const TaskDev T = task_of(a, i);
+        const SecDev S = sec_of(a, T.sec);
+        if (T.block * kPublish >= S.nsteps) continue;  // no such block (uniform)
+        if (threadIdx.x == 0) {
+            const bool ok = wait_block(a, S, T.block);
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            *flag = ok ? 1 : 0;
+        }
+        __syncthreads();
+        const bool ok = *flag != 0;
+        __syncthreads();
+        const int s0 = T.block * kPublish;
+        const int s1 = s0 + kPublish < S.nsteps ? s0 + kPublish : S.nsteps;
+        const int npair = (T.x1 - T.x0 + 1) / 2;
+        const int items = (s1 - s0) * npair;
+        for (int it = threadIdx.x; it < items; it += blockDim.x) {
+            const int st = s0 + it / npair;
+            const int x0 = T.x0 + 2 * (it % npair);
+            const float* p = S.part + (size_t)st * S.nw * S.ldp;
+            __attribute__((address_space(1))) double* row = as_global(S.rows + (size_t)st * S.nx);
+            // kRedDepth loads in flight per thread (the reads are latency-bound);
+            // rows past nw are clamped loads that are not added, so the sum
+            // runs over r in increasing order like k_rows
+            double a0 = 0.0, a1 = 0.0;
+            for (int r = 0; r < S.nw; r += kRedDepth) {
+                float2 v[kRedDepth];
+#pragma unroll
+                for (int j = 0; j < kRedDepth; ++j) {
+                    const int rr = r + j < S.nw ? r + j : S.nw - 1;
+                    v[j] = load_global(reinterpret_cast<const float2*>(p + (size_t)rr * S.ldp + x0));
+                }
+                __builtin_amdgcn_sched_barrier(0);  // every load issued before the first add
+#pragma unroll
+                for (int j = 0; j < kRedDepth; ++j)
+                    if (r + j < S.nw) {
+                        a0 += (double)v[j].x;
+                        a1 += (double)v[j].y;
+                    }
+            }
+            const double nan = __builtin_nan("");
+            row[x0] = ok ? a0 : nan;
+            if (x0 + 1 < T.x1) row[x0 + 1] = ok ? a1 : nan;
+        }
+        __syncthreads();  // *flag is reused by the next task
+    }
+}
+
+// Threads of a workgroup beyond its G sub-groups take no part in the work but
+// must meet every barrier of the active threads.
+__device__ __forceinline__ void idle_barriers(int n)
+{
+    for (int i = 0; i < n; ++i) __syncthreads();
+}
+
+}  // namespace
+}  // namespace mig
