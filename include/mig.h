@@ -355,7 +355,7 @@ MIG_API int mig_migrate_batched(const mig_section* secs, int32_t nsec,
  * 1 = register-tap kernel, two outputs per thread (N <= 35, nx <= 1024);
  * 3 = register-tap kernel, three outputs per thread (N <= 35, nx <= 1536);
  * 2 = register-tap kernel, four outputs per thread (N <= 35, nx <= 2048);
- * 0 = general kernel (taps read from the table every step); -1 = bad
+ * 0 = general kernel (any size; taps in registers where a wave allows); -1 = bad
  * arguments.  All kernels compute the same sums; results agree to FP32
  * rounding. */
 MIG_API int mig_kernel_kind(int32_t nx, int32_t ntaps);

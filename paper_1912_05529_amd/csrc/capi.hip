@@ -95,6 +95,9 @@ int reducer_count(int nprod, int want)
     return n < cap ? n : cap;
 }
 
+// Idle CUs from which on image rows are formed beside the depth stepping.
+constexpr int kReducerCus = 32;
+
 int blocks_of(int nsteps) { return (nsteps + kPublish - 1) / kPublish; }
 
 // x-parts per published block of a section: parts 32 points wide, so
@@ -237,10 +240,15 @@ int run_extrap(const float2* src, float2* dst, const float* vel, const double* o
         // Reducer workgroups form the rows of every published block but the
         // last, overlapped with the depth stepping; the last block, which
         // nothing is left to overlap with, is reduced after the launch by the
-        // whole GPU (launch_rows).
+        // whole GPU (launch_rows).  All rows are, where the frequency workgroups
+        // leave fewer than kReducerCus CUs (reducers then cannot keep pace, 31 GB/s
+        // each: 2000 points, 250 frequencies, 300 depths take 2.43 ms with 8 of
+        // them, 0.72 ms so), and in the general kernel (rows that no reducer waits
+        // for need not be written through: 845 against 977 us at 3001 points).
         const int nb = blocks_of(cs);
         a.rows = rows ? 1 : 0;
-        if (rows && nb > 1) {
+        const bool beside = rows && nb > 1 && kind != 0 && (tn.nred > 0 || device_cus() - nitems >= kReducerCus);
+        if (beside) {
             const int nred = reducer_count(nitems, tn.nred);
             a.parts = parts_of(nx);
             a.ntasks = (nb - 1) * a.parts;
@@ -258,7 +266,8 @@ int run_extrap(const float2* src, float2* dst, const float* vel, const double* o
             if (kind == 0) rc = launch_general(a, nx, s);
             else rc = launch_extrap(a, kind, G * threads_per_omega(kind, nx), s);
         }
-        if (rc == MIG_OK && rows) rc = launch_rows(part, a.one.rows, (nb - 1) * kPublish, cs, nx, nw, ldp, s);
+        if (rc == MIG_OK && rows)
+            rc = launch_rows(part, a.one.rows, beside ? (nb - 1) * kPublish : 0, cs, nx, nw, ldp, s);
         if (rc != MIG_OK) return rc;
         cur = mid;
     }

@@ -428,29 +428,41 @@ __global__ void k_index(const float* __restrict__ vel, const double* __restrict_
 
 
 // Image rows of depth steps [s0, s1) from their partial rows, once the
-// depth-stepping launch is over: one thread per point, the frequencies added in
+// depth-stepping launch is over: four points per thread, the frequencies added in
 // increasing order in FP64, the order of the reducer workgroups, so a row is the
 // same whichever of the two forms it.  Small workgroups spread the rows over
-// every CU; 16 loads in flight per thread.
+// every CU; 16 loads of 16 bytes in flight per thread (row strides are multiples of 256
+// points; the last thread of a row reads its padding, which frequency workgroups of
+// odd widths leave unwritten, and does not store those sums).
 __global__ void __launch_bounds__(64) k_rows(const float* __restrict__ part,
                                              double* __restrict__ rows, int s0, int nx, int nw,
                                              int ldp)
 {
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
+    typedef float v4f __attribute__((ext_vector_type(4)));
+    const int x = 4 * (blockIdx.x * blockDim.x + threadIdx.x);
     if (x >= nx) return;
     const int st = s0 + blockIdx.y;
     const float* p = part + (size_t)st * nw * ldp + x;
-    double acc = 0.0;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    const auto add = [&](const v4f& v) {
+        acc[0] += (double)v.x;
+        acc[1] += (double)v.y;
+        acc[2] += (double)v.z;
+        acc[3] += (double)v.w;
+    };
     int r = 0;
     for (; r + 16 <= nw; r += 16) {
-        float v[16];
+        v4f v[16];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) v[j] = p[(size_t)(r + j) * ldp];
+        for (int j = 0; j < 16; ++j) v[j] = *reinterpret_cast<const v4f*>(p + (size_t)(r + j) * ldp);
 #pragma unroll
-        for (int j = 0; j < 16; ++j) acc += (double)v[j];
+        for (int j = 0; j < 16; ++j) add(v[j]);
     }
-    for (; r < nw; ++r) acc += (double)p[(size_t)r * ldp];
-    rows[(size_t)st * nx + x] = acc;
+    for (; r < nw; ++r) add(*reinterpret_cast<const v4f*>(p + (size_t)r * ldp));
+    double* row = rows + (size_t)st * nx + x;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        if (x + q < nx) row[q] = acc[q];
 }
 
 template <int M>
@@ -550,7 +562,7 @@ int launch_rows(const float* part, double* rows, int s0, int s1, int nx, int nw,
                 hipStream_t s)
 {
     if (s1 <= s0) return MIG_OK;
-    dim3 grid((nx + 63) / 64, s1 - s0);
+    dim3 grid((nx + 255) / 256, s1 - s0);
     hipLaunchKernelGGL(k_rows, grid, dim3(64), 0, s, part, rows, s0, nx, nw, ldp);
     return hipGetLastError() == hipSuccess ? MIG_OK : MIG_E_DEVICE;
 }

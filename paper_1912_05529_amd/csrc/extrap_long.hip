@@ -16,7 +16,7 @@
 //
 // Bound by the FP32 instruction rate of the CUs that hold a workgroup (a multiply-add
 // occupies a SIMD for 4 cycles, an add for 2).  3001 points, 101 frequencies, 300 depths,
-// 35 taps, layered: 6430 -> TLONG us (before: 256 threads, one output at a time, its taps
+// 35 taps, layered, without the rows' sum: 6430 -> 760 us (before: 256 threads, one output at a time, its taps
 // read from the table every step).
 #include <type_traits>
 #include <utility>
@@ -183,9 +183,36 @@ __global__ void __launch_bounds__(kLongThreads) k_extrap_long(BatchArgs a)
     slowness(S.slow, 0, v);
     update(v, true);
     __syncthreads();
+    // Memory operations of a step: the partial row of the step before, the next row's
+    // slowness (both at its start), the taps that follow from it (at its end).  The one
+    // wait at the start of a step finds all but those taps long complete; a row stored
+    // at the end of its own step would be waited for by the next update (a
+    // write-through to memory: 1125 against 977 us at 3001 points with reducers beside).
+    float re[Q] = {};    // real parts of the last step's outputs (one run only)
+    const auto store_row = [&](int k, int x0, const float (&v)[Q]) {
+        if (x0 < nx) {  // the row stride holds whole runs of Q
+            float* pr = S.part + ((size_t)k * nw + r) * S.ldp + x0;
+            // Without reducers in the launch nobody reads the rows before its end: one
+            // streaming store (write-through pairs 1026, plain 869, streaming 845 us
+            // with the rows summed after the launch, 749 without rows).
+            if (a.nred > 0) {
+#pragma unroll
+                for (int q = 0; q < Q; q += 2) store_partial2(pr + q, v[q], v[q + 1]);
+            } else if constexpr (Q == 4) {
+                __builtin_nontemporal_store(v4f{v[0], v[1], v[2], v[3]}, as_global(reinterpret_cast<v4f*>(pr)));
+            } else {
+                typedef float v2f __attribute__((ext_vector_type(2)));
+                __builtin_nontemporal_store(v2f{v[0], v[1]}, as_global(reinterpret_cast<v2f*>(pr)));
+            }
+        }
+    };
     for (int k = 0; k < S.nsteps; ++k) {
-        // the next row's slowness (flagged where it differs from this row's)
-        if (nrun == 1) slowness(S.slow + (size_t)(k + 1 < S.nsteps ? k + 1 : k) * S.ldp, 0, v);
+        wait_vmem_all();
+        if (nrun == 1) {
+            if (rows_on && k >= 1) store_row(k - 1, Q * t, re);
+            // flagged where it differs from this row's
+            slowness(S.slow + (size_t)(k + 1 < S.nsteps ? k + 1 : k) * S.ldp, 0, v);
+        }
         for (int s = 0; s < nrun; ++s) {
             const int x0 = Q * (t + s * T);
             if (__builtin_amdgcn_readfirstlane(x0) >= nx) break;  // the whole wave is past nx
@@ -208,19 +235,21 @@ __global__ void __launch_bounds__(kLongThreads) k_extrap_long(BatchArgs a)
             }
             float2* dst = sm + ((k + 1) & 1) * LB + H + x0;
 #pragma unroll
-            for (int q = 0; q < Q; ++q)
+            for (int q = 0; q < Q; ++q) {
                 if (x0 + q < nx) dst[q] = o[q];
-            if (rows_on && x0 < nx) {  // the row stride holds whole runs of Q
-                float* pr = S.part + ((size_t)k * nw + r) * S.ldp + x0;
-#pragma unroll
-                for (int q = 0; q < Q; q += 2) store_partial2(pr + q, o[q].x, o[q + 1].x);
+                re[q] = o[q].x;
             }
+            if (nrun > 1 && rows_on) store_row(k, x0, re);
         }
         if (nrun == 1 && k + 1 < S.nsteps) update(v, false);
-        const bool publish = rows_on && ((k + 1) % kPublish == 0 || k + 1 == S.nsteps);
-        if (publish) wait_vmem_all();
         __syncthreads();
-        if (publish) publish_block(a, S, k / kPublish);
+        if (rows_on && publishes_at(k)) publish_block(a, S, k / kPublish - 1);
+    }
+    if (rows_on) {
+        if (nrun == 1) store_row(S.nsteps - 1, Q * t, re);
+        wait_vmem_all();
+        __syncthreads();
+        for (int b = published_in_loop(S.nsteps); b * kPublish < S.nsteps; ++b) publish_block(a, S, b);
     }
     if (S.wout) {
         const float2* src = sm + (S.nsteps & 1) * LB + H;
