@@ -274,11 +274,12 @@ MIG_API int mig_transform_t(const float* section, int32_t nx, int32_t nt,
  *     data = Q_0,
  * where j(x, k) is the table entry of (omega_r, vel[k][x]).  FP32 complex
  * arithmetic, one workgroup per frequency walking the depth steps backwards.
- * For nx <= 1024 and N <= 35 the step is the FIR with each point's own
- * conjugated taps plus exact corrections where the velocity changes along x
- * (at most 16 such points per row; otherwise, and for nk > 65536, a kernel
- * that forms every product conj(h_j(y)[m]) q[y] runs instead); results agree
- * to FP32 rounding either way and are run-to-run identical.
+ * For nx <= 1536, 3 <= N <= 35 and nk <= 65536 the step is the FIR with each
+ * point's own conjugated taps plus exact corrections where the velocity
+ * changes along x, if no row has more than 16 such points.  Otherwise the FIR
+ * with one entry's taps where all points that it reaches share the entry, and
+ * every product conj(h_j(y)[m]) q[y] elsewhere.  Results agree to FP32
+ * rounding either way and are run-to-run identical.
  *   image [nz][nx] float64 (in), vel [nz][nx] float32 (in; row nz-1 unused),
  *   omega [nw] float64 (in), tab32 [nk][M+1] complex64 (in),
  *   data  [nx][nw] complex64 (out), ws >= mig_demigrate_workspace_size bytes

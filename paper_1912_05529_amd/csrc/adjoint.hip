@@ -8,14 +8,14 @@
 //     (E_k^H q)[x] = sum_{n=-M..M} conj(h_{j(x+n,k)}[|n|]) q[x+n]:
 // every point x+n contributes through the filter of that point.  A workgroup
 // owns one frequency for all depths (walking them backwards).  Three kernels:
-//   * folded (nx <= 1024, N <= 35, at most 16 lateral velocity changes per
+//   * folded (nx <= 1536, N <= 35, at most 16 lateral velocity changes per
 //     row): the Eq. (1) FIR with each point's own conjugated taps plus exact
 //     corrections around the points where the filter changes along x (see
 //     the derivation before k_demigrate_fold);
-//   * product (same sizes, any velocity; runs when some row has more change
-//     points): per step it forms g_m[y] = conj(h_{j(y)}[m]) q[y] for its
+//   * product (nx <= 1024, N <= 35, any velocity; runs when some row has more
+//     change points): per step it forms g_m[y] = conj(h_{j(y)}[m]) q[y] for its
 //     points in LDS and gathers out[x] = g_0[x] + sum_m (g_m[x-m] + g_m[x+m]);
-//   * general (any size): the product form a chunk of taps at a time.
+//   * general (adjoint_long.hip): any size and velocity; runs where the other two do not.
 #include "common.hpp"
 
 namespace mig {
@@ -25,57 +25,6 @@ __device__ __forceinline__ float2 cmul_conj(float2 h, float2 q)
 {
     // conj(h) * q
     return make_float2(fmaf(h.y, q.y, h.x * q.x), fmaf(-h.y, q.x, h.x * q.y));
-}
-
-__global__ void __launch_bounds__(512) k_demigrate(AdjArgs a)
-{
-    extern __shared__ float4 smem4[];
-    float2* Q = reinterpret_cast<float2*>(smem4);          // [nx]
-    float2* acc = Q + a.nx;                                 // [nx]
-    float2* Gm = acc + a.nx;                                // [C][nx + 2M], zero borders
-    const int M = a.M, nx = a.nx, nw = a.nw, C = a.chunk;
-    const int LG = nx + 2 * M;
-    const int r = blockIdx.x;
-    const double ar = a.omega[r] / a.dk;
-
-    for (int i = threadIdx.x; i < C * LG; i += blockDim.x) Gm[i] = make_float2(0.0f, 0.0f);
-    for (int x = threadIdx.x; x < nx; x += blockDim.x)
-        Q[x] = make_float2((float)a.image[(size_t)(a.nz - 1) * nx + x], 0.0f);
-    __syncthreads();
-
-    for (int k = a.nz - 2; k >= 0; --k) {
-        const double* srow = a.slow + (size_t)k * a.ldp;
-        for (int x = threadIdx.x; x < nx; x += blockDim.x)
-            acc[x] = make_float2((float)a.image[(size_t)k * nx + x], 0.0f);
-        for (int m0 = 0; m0 <= M; m0 += C) {
-            const int m1 = m0 + C <= M + 1 ? m0 + C : M + 1;
-            for (int y = threadIdx.x; y < nx; y += blockDim.x) {
-                const float2* h = a.tab + (size_t)index_of_slowness(ar, a.b, a.nk,
-                                                                    slowness_value(srow[y])) * (M + 1);
-                const float2 q = Q[y];
-                for (int m = m0; m < m1; ++m) Gm[(m - m0) * LG + M + y] = cmul_conj(h[m], q);
-            }
-            __syncthreads();
-            for (int x = threadIdx.x; x < nx; x += blockDim.x) {
-                float2 s = acc[x];
-                for (int m = m0; m < m1; ++m) {
-                    const float2* g = Gm + (m - m0) * LG + M + x;
-                    if (m == 0) {
-                        s.x += g[0].x;
-                        s.y += g[0].y;
-                    } else {
-                        s.x += g[-m].x + g[m].x;
-                        s.y += g[-m].y + g[m].y;
-                    }
-                }
-                acc[x] = s;
-            }
-            __syncthreads();
-        }
-        for (int x = threadIdx.x; x < nx; x += blockDim.x) Q[x] = acc[x];
-        __syncthreads();
-    }
-    for (int x = threadIdx.x; x < nx; x += blockDim.x) a.out[(size_t)x * nw + r] = Q[x];
 }
 
 // Register-tap form (nx <= 2 * kAdjThreads, M <= kAdjMaxM): each thread owns
@@ -411,12 +360,12 @@ __device__ __forceinline__ void fold2(const float2* __restrict__ win, const floa
 {
     constexpr int P = M / 2;
     const float4* w4 = reinterpret_cast<const float4*>(win);
-    float2 a0 = make_float2(0.0f, 0.0f), a1 = a0;
+    float2 a0 = make_float2(0.0f, 0.0f), a1 = a0, b0 = a0, b1 = a0;  // a sum per pass: shorter chains
     fold2_pass<M, 0, P>(w4, h0, h1, a0, a1);
     __builtin_amdgcn_sched_barrier(0);
-    fold2_pass<M, P + 1, M>(w4, h0, h1, a0, a1);
-    o0 = a0;
-    o1 = a1;
+    fold2_pass<M, P + 1, M>(w4, h0, h1, b0, b1);
+    o0 = make_float2(a0.x + b0.x, a0.y + b0.y);
+    o1 = make_float2(a1.x + b1.x, a1.y + b1.y);
 }
 
 // LDS of the folded kernel: two planes, a row of corrections per wave (its
@@ -636,8 +585,13 @@ __device__ __forceinline__ void fold_step(const AdjArgs& a, float2* sm, float4* 
     __syncthreads();
 }
 
-template <int M>
-__global__ void __launch_bounds__(512) k_demigrate_fold(AdjArgs a)
+// Up to 512 threads (1024 points), or 768: three waves per SIMD within 168 registers (up
+// to 1536 points; a fourth would spill).  1501 points, 101 frequencies, 300 depths, 35
+// taps, layered: 3630 -> 752 us (before: the general kernel, now 982 there).
+constexpr int kFoldMaxThreads = 768;
+
+template <int M, int THREADS>
+__global__ void __launch_bounds__(THREADS) k_demigrate_fold(AdjArgs a)
 {
     if (*as_global(a.dense) != 0) return;  // uniform: the product kernel runs
     extern __shared__ float4 smem4[];
@@ -708,17 +662,23 @@ __global__ void __launch_bounds__(512) k_demigrate_fold(AdjArgs a)
     if (F.ok1) a.out[(size_t)(F.x0 + 1) * a.nw + r] = P0[F.x0 + 1];
 }
 
+template <int M, int THREADS>
+int launch_fold_as(const AdjArgs& a, int tsub, hipStream_t s)
+{
+    const size_t lds = fold_lds(tsub, M);
+    if (lds > 65536 &&
+        hipFuncSetAttribute(reinterpret_cast<const void*>(&k_demigrate_fold<M, THREADS>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        return MIG_E_DEVICE;
+    hipLaunchKernelGGL((k_demigrate_fold<M, THREADS>), dim3(a.nw), dim3(tsub), lds, s, a);
+    return hipGetLastError() == hipSuccess ? MIG_OK : MIG_E_DEVICE;
+}
+
 template <int M>
 int launch_fold(const AdjArgs& a, hipStream_t s)
 {
     const int tsub = ((a.nx + 1) / 2 + 63) / 64 * 64;
-    const size_t lds = fold_lds(tsub, M);
-    if (lds > 65536 &&
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&k_demigrate_fold<M>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-        return MIG_E_DEVICE;
-    hipLaunchKernelGGL(k_demigrate_fold<M>, dim3(a.nw), dim3(tsub), lds, s, a);
-    return hipGetLastError() == hipSuccess ? MIG_OK : MIG_E_DEVICE;
+    return tsub <= 512 ? launch_fold_as<M, 512>(a, tsub, s) : launch_fold_as<M, kFoldMaxThreads>(a, tsub, s);
 }
 
 // Change-point pre-pass, one workgroup per depth row: the first wave lists the
@@ -796,7 +756,7 @@ int launch_demigrate_reg(const AdjArgs& a, hipStream_t s)
 
 bool adjoint_uses_fold(int nx, int M)
 {
-    return nx <= 2 * kAdjThreads && M >= 1 && M <= kAdjMaxM && adjoint_fold_kmax(nx, M) >= 1;
+    return nx <= 2 * kFoldMaxThreads && M >= 1 && M <= kAdjMaxM && adjoint_fold_kmax(nx, M) >= 1;
 }
 
 int adjoint_fold_kmax(int nx, int M)
@@ -825,27 +785,6 @@ int launch_demigrate_fold(const AdjArgs& a, hipStream_t s)
 #undef MIG_FOLD_CASE
     default: return MIG_E_ARG;
     }
-}
-
-int adjoint_chunk(int nx, int M, size_t lds_limit)
-{
-    // LDS = (2 nx + C (nx + 2M)) complex64
-    long long room = (long long)(lds_limit / sizeof(float2)) - 2LL * nx;
-    long long c = room / (nx + 2 * M);
-    if (c > M + 1) c = M + 1;
-    return (int)(c < 1 ? 0 : c);
-}
-
-int launch_demigrate(const AdjArgs& a, hipStream_t s)
-{
-    size_t lds = (size_t)(2 * a.nx + a.chunk * (a.nx + 2 * a.M)) * sizeof(float2);
-    if (lds > 65536) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_demigrate),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-            return MIG_E_DEVICE;
-    }
-    hipLaunchKernelGGL(k_demigrate, dim3(a.nw), dim3(512), lds, s, a);
-    return hipGetLastError() == hipSuccess ? MIG_OK : MIG_E_DEVICE;
 }
 
 }  // namespace mig

@@ -760,9 +760,7 @@ MIG_API int mig_demigrate(const double* image, const float* vel, const double* o
     const int M = (d->ntaps - 1) / 2;
     AdjArgs a = {};
     const bool reg = adjoint_uses_registers(nx, M, (size_t)lds_max);
-    const bool fold = reg && nz > 1 && d->nk <= 65536 && adjoint_uses_fold(nx, M);
-    a.chunk = adjoint_chunk(nx, M, (size_t)lds_max);
-    if (!reg && a.chunk < 1) return MIG_E_ARG;
+    const bool fold = nz > 1 && d->nk <= 65536 && adjoint_uses_fold(nx, M);
     hipStream_t s = as_stream(stream);
     char* base = static_cast<char*>(ws);
     const size_t rows = nz > 1 ? (size_t)(nz - 1) : 1;
@@ -805,15 +803,14 @@ MIG_API int mig_demigrate(const double* image, const float* vel, const double* o
         int rc = launch_slowness(sa, nz - 1, a.ldp, -1, s);
         if (rc != MIG_OK) return rc;
     }
-    if (!reg) return launch_demigrate(a, s);
     if (fold) {
         // the folded kernel runs unless some row has more change points than
-        // it handles; the product kernel, launched after it, runs only then
+        // it handles; the kernel launched after it runs only then
         int rc = launch_adj_changes(a, s);
         if (rc == MIG_OK) rc = launch_demigrate_fold(a, s);
         if (rc != MIG_OK) return rc;
     }
-    return launch_demigrate_reg(a, s);
+    return reg ? launch_demigrate_reg(a, s) : launch_demigrate(a, s);
 }
 
 MIG_API size_t mig_transform_workspace_size(int32_t nt, int32_t nw)

@@ -105,7 +105,6 @@ struct AdjArgs {
     int* dense;
     int kmax;
     int nx, nz, nw, ldp, nk, M;
-    int chunk;             // filter taps handled per LDS pass
     double dk, b;
 };
 
@@ -210,8 +209,7 @@ inline int flag_distance(int kind) { return kind == 1 ? 2 : 1; }
 // `kind` and `threads` (workgroup size) are the same for all items.
 int launch_extrap(const BatchArgs& a, int kind, int threads, hipStream_t s);
 int launch_general(const BatchArgs& a, int max_nx, hipStream_t s);
-// Taps per LDS pass of the demigration kernel for an LDS budget (0 = too big).
-int adjoint_chunk(int nx, int M, size_t lds_limit);
+// Adjoint of wide sections and long filters (any size).
 int launch_demigrate(const AdjArgs& a, hipStream_t s);
 // Register-tap adjoint kernel: usable for these sizes within an LDS budget?
 bool adjoint_uses_registers(int nx, int M, size_t lds_limit);

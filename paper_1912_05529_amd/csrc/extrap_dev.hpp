@@ -194,5 +194,56 @@ __device__ __forceinline__ void idle_barriers(int n)
     for (int i = 0; i < n; ++i) __syncthreads();
 }
 
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v4f_a8 __attribute__((ext_vector_type(4), aligned(8)));
+
+// Halo of the planes on each side: M rounded up to whole 16-byte reads.
+__host__ __device__ constexpr int long_halo(int M) { return (M + 1) & ~1; }
+// Points of one plane with its halos; lanes read whole runs of Q <= 4 outputs.
+__host__ __device__ constexpr int long_plane(int nx, int M) { return (nx + 3) / 4 * 4 + 2 * long_halo(M); }
+
+// The window around outputs P[0 .. Q-1]: w[PM + i] = P[i].
+template <int M, int Q>
+struct Window {
+    static constexpr int PM = long_halo(M);
+    // pairs of taps whose points are read ahead of their use (three: 3 % slower)
+    static constexpr int kAhead = 1;
+    static constexpr int NP = (M + 1) / 2;
+    float2 w[2 * PM + Q];
+    const float2* P;
+    __device__ __forceinline__ void load(int i)  // points i, i + 1 (i even)
+    {
+        const v4f q = *reinterpret_cast<const v4f*>(P + i);
+        w[PM + i] = make_float2(q.x, q.y);
+        w[PM + i + 1] = make_float2(q.z, q.w);
+    }
+    // the points that taps 2 i + 1 and 2 i + 2 reach beyond those of smaller taps
+    __device__ __forceinline__ void load_pair(int i)
+    {
+        if (i < NP) {
+            load(-(2 * i + 2));
+            load(2 * i + Q);
+        }
+    }
+    // the outputs' own points and the first pairs
+    __device__ __forceinline__ void begin()
+    {
+#pragma unroll
+        for (int i = 0; i < Q; i += 2) load(i);
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) load_pair(i);
+    }
+    __device__ __forceinline__ float2 pair_sum(int q, int n) const { return cadd(w[PM + q - n], w[PM + q + n]); }
+};
+
+// Two consecutive taps of a table row (the second may lie past its end where unused).
+__device__ __forceinline__ v4f tap_pair(const float2* row, int n, bool two)
+{
+    typedef const __attribute__((address_space(1))) v4f_a8* global_v4f;
+    if (two) return *(global_v4f)reinterpret_cast<const v4f_a8*>(row + n);
+    const float2 a = load_global(row + n);
+    return v4f{a.x, a.y, 0.0f, 0.0f};
+}
+
 }  // namespace
 }  // namespace mig

@@ -26,36 +26,7 @@
 namespace mig {
 namespace {
 
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef float v4f_a8 __attribute__((ext_vector_type(4), aligned(8)));
-
 constexpr int kLongThreads = 768;  // three waves per SIMD: up to 168 registers
-
-// Halo of the planes on each side: M rounded up to whole 16-byte reads.
-__host__ __device__ constexpr int long_halo(int M) { return (M + 1) & ~1; }
-// Points of one plane with its halos; lanes read whole runs of Q <= 4 outputs.
-__host__ __device__ constexpr int long_plane(int nx, int M) { return (nx + 3) / 4 * 4 + 2 * long_halo(M); }
-
-// The window around outputs P[0 .. Q-1]: w[PM + i] = P[i].
-template <int M, int Q>
-struct Window {
-    static constexpr int PM = long_halo(M);
-    float2 w[2 * PM + Q];
-    const float2* P;
-    __device__ __forceinline__ void load(int i)  // points i, i + 1 (i even)
-    {
-        const v4f q = *reinterpret_cast<const v4f*>(P + i);
-        w[PM + i] = make_float2(q.x, q.y);
-        w[PM + i + 1] = make_float2(q.z, q.w);
-    }
-    // the points that taps 2 i + 1 and 2 i + 2 reach beyond those of smaller taps
-    __device__ __forceinline__ void load_pair(int i)
-    {
-        load(-(2 * i + 2));
-        load(2 * i + Q);
-    }
-    __device__ __forceinline__ float2 pair_sum(int q, int n) const { return cadd(w[PM + q - n], w[PM + q + n]); }
-};
 
 // Q outputs with the lane's taps h.
 template <int M, int Q>
@@ -63,29 +34,18 @@ __device__ __forceinline__ void fir_shared(const float2* P, const float2 (&h)[M 
 {
     Window<M, Q> W;
     W.P = P;
-#pragma unroll
-    for (int i = 0; i < Q; i += 2) W.load(i);
-    if constexpr (M > 0) W.load_pair(0);
+    W.begin();
 #pragma unroll
     for (int q = 0; q < Q; ++q) o[q] = cmulf(h[0], W.w[W.PM + q]);
 #pragma unroll
     for (int i = 0; i < (M + 1) / 2; ++i) {
-        if (i + 1 < (M + 1) / 2) W.load_pair(i + 1);
+        W.load_pair(i + W.kAhead);
 #pragma unroll
         for (int n = 2 * i + 1; n <= (2 * i + 2 < M ? 2 * i + 2 : M); ++n)
 #pragma unroll
             for (int q = 0; q < Q; ++q) o[q] = cfmaf(h[n], W.pair_sum(q, n), o[q]);
         __builtin_amdgcn_sched_barrier(0);
     }
-}
-
-// Two consecutive taps of a table row (the second may lie past its end where unused).
-__device__ __forceinline__ v4f tap_pair(const float2* row, int n, bool two)
-{
-    typedef const __attribute__((address_space(1))) v4f_a8* global_v4f;
-    if (two) return *(global_v4f)reinterpret_cast<const v4f_a8*>(row + n);
-    const float2 a = load_global(row + n);
-    return v4f{a.x, a.y, 0.0f, 0.0f};
 }
 
 // Q outputs, each with the taps of its own table row.
@@ -102,9 +62,7 @@ __device__ __forceinline__ void fir_mixed(const float2* P, const float2* (&row)[
     if (M > 0)
 #pragma unroll
         for (int q = 0; q < Q; ++q) hp[0][q] = tap_pair(row[q], 1, M >= 2);
-#pragma unroll
-    for (int i = 0; i < Q; i += 2) W.load(i);
-    if constexpr (M > 0) W.load_pair(0);
+    W.begin();
 #pragma unroll
     for (int q = 0; q < Q; ++q) o[q] = cmulf(h0[q], W.w[W.PM + q]);
 #pragma unroll
@@ -112,8 +70,8 @@ __device__ __forceinline__ void fir_mixed(const float2* P, const float2* (&row)[
         if (i + 1 < NP) {
 #pragma unroll
             for (int q = 0; q < Q; ++q) hp[(i + 1) & 1][q] = tap_pair(row[q], 2 * i + 3, 2 * i + 4 <= M);
-            W.load_pair(i + 1);
         }
+        W.load_pair(i + W.kAhead);
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             const v4f h = hp[i & 1][q];
