@@ -353,7 +353,7 @@ MIG_API int mig_migrate_batched(const mig_section* secs, int32_t nsec,
                                 size_t ws_bytes, void* stream);
 
 /* Diagnostic query: which extrapolation kernel a call with these sizes takes.
- * 1 = register-tap kernel, two outputs per thread (N <= 35, nx <= 1024);
+ * 1 = register-tap kernel, one or two outputs per thread (N <= 35, nx <= 1024);
  * 3 = register-tap kernel, three outputs per thread (N <= 35, nx <= 1536);
  * 2 = register-tap kernel, four outputs per thread (N <= 35, nx <= 2048);
  * 0 = general kernel (any size; taps in registers where a wave allows); -1 = bad

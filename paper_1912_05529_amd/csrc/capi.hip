@@ -264,7 +264,9 @@ int run_extrap(const float2* src, float2* dst, const float* vel, const double* o
         int rc = launch_slowness(a, cs, ldp, flag_distance(kind), s);
         if (rc == MIG_OK) {
             if (kind == 0) rc = launch_general(a, nx, s);
-            else rc = launch_extrap(a, kind, G * threads_per_omega(kind, nx), s);
+            else if (extrap_narrow(kind, nx, G, nitems, device_cus()))
+                rc = launch_extrap(a, kind, G * threads_narrow(nx), true, s);
+            else rc = launch_extrap(a, kind, G * threads_per_omega(kind, nx), false, s);
         }
         if (rc == MIG_OK && rows)
             rc = launch_rows(part, a.one.rows, beside ? (nb - 1) * kPublish : 0, cs, nx, nw, ldp, s);
@@ -508,7 +510,7 @@ int run_batch(const mig_section* secs, int nsec, const float2* tab, const mig_ta
         int rc = launch_slowness(a, g.max_rows, g.max_ldp, flag_distance(g.kind), s);
         if (rc == MIG_OK) {
             if (g.kind == 0) rc = launch_general(a, g.max_nx, s);
-            else rc = launch_extrap(a, g.kind, g.threads, s);
+            else rc = launch_extrap(a, g.kind, g.threads, false, s);
         }
         if (rc != MIG_OK) return rc;
     }

@@ -166,9 +166,9 @@ __device__ __forceinline__ int index_of_slowness(double a, double b, int nk, dou
     double t = a * s;
     t = t - b;
     double u = t + 0.5;
-    if (!(u >= 1.0)) return 0;
-    if (u >= (double)nk) return nk - 1;
-    return (int)floor(u);
+    // below 1 and NaN: 0; nk and above: nk - 1; else the integer part
+    u = __builtin_fmin(__builtin_fmax(u, 0.0), (double)nk - 0.5);
+    return (int)u;
 }
 
 __device__ __forceinline__ int table_index(double a, double b, int nk, float v)
@@ -181,13 +181,16 @@ __device__ __forceinline__ int table_index(double a, double b, int nk, float v)
 inline int row_stride(int nx) { return (nx + 255) / 256 * 256; }
 
 // Kernel variants (tests and the benchmark can query which one runs):
-// 1 = register taps, two outputs per thread, two tap sets (nx <= 1024);
+// 1 = register taps, one or two outputs per thread, two tap sets (nx <= 1024);
 // 3 = register taps, three outputs per thread, one tap set (nx <= 1536);
 // 2 = register taps, four outputs per thread, one tap set (nx <= 2048);
 // 0 = general kernel (any size), taps in registers or read from the table by wave.
 int extrap_kernel_kind(int nx, int M);
 // Threads one frequency needs in kernel `kind` for nx points.
 int threads_per_omega(int kind, int nx);
+// Kernel 1 with one output per thread, in a launch of one section, and its threads.
+bool extrap_narrow(int kind, int nx, int G, int nitems, int cus);
+int threads_narrow(int nx);
 
 // Host launchers (return MIG_OK or MIG_E_DEVICE).
 int launch_design_basis(const mig_table_desc* d, double* A, double* C, hipStream_t s);
@@ -207,7 +210,7 @@ int launch_slowness(const BatchArgs& a, int max_rows, int max_ldp, int dist, hip
 inline int flag_distance(int kind) { return kind == 1 ? 2 : 1; }
 // Depth stepping for every workgroup item (+ reducers when sections want rows).
 // `kind` and `threads` (workgroup size) are the same for all items.
-int launch_extrap(const BatchArgs& a, int kind, int threads, hipStream_t s);
+int launch_extrap(const BatchArgs& a, int kind, int threads, bool narrow, hipStream_t s);
 int launch_general(const BatchArgs& a, int max_nx, hipStream_t s);
 // Adjoint of wide sections and long filters (any size).
 int launch_demigrate(const AdjArgs& a, hipStream_t s);

@@ -18,11 +18,10 @@
 //     velocity under it changes (omega is fixed per sub-group), which in
 //     layered media is a few times per column.  Two register sets alternate
 //     between even and odd steps; the set for step k+1 is refilled during step
-//     k only for outputs whose slowness changed, so table reads (L2-resident)
-//     are rare and their latency is hidden behind a full step of arithmetic.
-//     All vector-memory operations of a step are issued at its start (last
-//     step's partial row, refills, slowness prefetch), so one wait at the top
-//     of the next step finds them long complete.
+//     k, by waves some output of which changes its slowness.  The loads stand
+//     between the stages of the FIR, whose arithmetic hides them; the slowness
+//     is read two steps ahead, and a partial row is stored at the end of its
+//     step and first waited for a step later.
 //   * The look-up needs 1/v in FP64; it is computed once per (depth, x) by a
 //     small pre-pass (shared by all frequencies) instead of once per refill.
 //   * The image row needs a sum over frequencies, i.e. across workgroups.
@@ -53,65 +52,86 @@ __device__ __forceinline__ void load_taps(float2 (&h)[M + 1], const float2* __re
     for (int n = 0; n <= M; ++n) h[n] = row[n];
 }
 
-// Two outputs x0, x0+1 from the window w[i] = P[x0 - M + i], i = 0..2M+1.
-template <int M>
-__device__ __forceinline__ void fir2(const float2* __restrict__ win, const float2 (&h0)[M + 1],
-                                     const float2 (&h1)[M + 1], float2& o0, float2& o1)
-{
-    float2 w[2 * M + 2];
-    const float4* w4 = reinterpret_cast<const float4*>(win);
-#pragma unroll
-    for (int i = 0; i <= M; ++i) {
-        float4 q = w4[i];
-        w[2 * i] = make_float2(q.x, q.y);
-        w[2 * i + 1] = make_float2(q.z, q.w);
-    }
-    float2 a0 = cmulf(h0[0], w[M]);
-    float2 a1 = cmulf(h1[0], w[M + 1]);
-#pragma unroll
-    for (int n = 1; n <= M; ++n) {
-        a0 = cfmaf(h0[n], cadd(w[M - n], w[M + n]), a0);
-        a1 = cfmaf(h1[n], cadd(w[M + 1 - n], w[M + 1 + n]), a1);
-    }
-    o0 = a0;
-    o1 = a1;
-}
+// Stages of the FIR between two groups of tap refills (a branch each: one group per stage
+// costs waves that refill nothing 3 %; a FIR of its own for waves that refill makes the
+// compiler move whole tap sets where the two meet).
+constexpr int kRefillStages = 3;
 
-// Q adjacent outputs x0..x0+Q-1 from the window w[i] = P[x0 - M + i],
-// i = 0..2M+Q-1.  Even Q: x0 is even, so the window is read with 16-byte LDS
-// loads; odd Q (x0 of either parity): 8-byte loads.
+// Q adjacent outputs x0..x0+Q-1 from the window w[i] = P[x0 - M + i], i = 0..2M+Q-1.
+// Even Q: x0 is even, so the window is read with 16-byte LDS loads; odd Q (x0 of either
+// parity): 8-byte loads.  Points are read from the centre outwards, as the taps use them
+// (two taps per stage), kStagesAhead stages before their use: after a barrier every wave
+// of the CU reads at once, and a wave that asked for its whole window first would leave
+// the SIMDs idle until most of the CU's reads were done (1024 points, 300 depths, 150
+// frequencies, constant velocity: 280 -> 261 us).
+constexpr int kStagesAhead = 2;
+
 template <int M, int Q>
+constexpr int kCentre = Q % 2 == 0 && M % 2 ? 1 : 0;  // last tap of stage 0
+template <int M, int Q>
+constexpr int kStages = (M - kCentre<M, Q> + 1) / 2;  // stages after stage 0
+
+template <int M, int Q, class F>
 __device__ __forceinline__ void firq(const float2* __restrict__ win, const float2 (&h)[Q][M + 1],
-                                     float2 (&o)[Q])
+                                     float2 (&o)[Q], const F& beside)
 {
+    // Stage 0: points M - E .. M + Q - 1 + E, for taps 0 .. E.  Stage s: two points more on
+    // each side, for two taps more (the outermost may be cut short by the window's ends).
+    constexpr int E = kCentre<M, Q>, NS = kStages<M, Q>;
     float2 w[2 * M + Q];
-    if constexpr (Q % 2 == 0) {
-        const float4* w4 = reinterpret_cast<const float4*>(win);
-#pragma unroll
-        for (int i = 0; i < M + Q / 2; ++i) {
-            float4 q = w4[i];
-            w[2 * i] = make_float2(q.x, q.y);
-            w[2 * i + 1] = make_float2(q.z, q.w);
+    const auto load = [&](int i) {  // points i, i + 1 (i even where Q is)
+        if constexpr (Q % 2 == 0) {
+            const float4 q = *reinterpret_cast<const float4*>(win + i);
+            w[i] = make_float2(q.x, q.y);
+            w[i + 1] = make_float2(q.z, q.w);
+        } else {
+            if (i >= 0 && i < 2 * M + Q) w[i] = win[i];
+            if (i + 1 >= 0 && i + 1 < 2 * M + Q) w[i + 1] = win[i + 1];
         }
-    } else {
+    };
+    const auto stage = [&](int s) {
+        if (s > NS) return;
+        load(M - E - 2 * s);
+        load(M + Q - 2 + E + 2 * s);
+    };
 #pragma unroll
-        for (int i = 0; i < 2 * M + Q; ++i) w[i] = win[i];
+    for (int i = M - E; i < M + Q + E; i += 2) {
+        if (Q % 2 == 0 || i + 1 < M + Q) load(i);
+        else w[i] = win[i];
     }
+#pragma unroll
+    for (int s = 1; s <= kStagesAhead; ++s) stage(s);
 #pragma unroll
     for (int q = 0; q < Q; ++q) o[q] = cmulf(h[q][0], w[M + q]);
+    // (the outputs are pinned: left alone, the compiler sums one after the other and keeps
+    // the whole window in registers for it)
+    const auto tap = [&](int n) {
 #pragma unroll
-    for (int n = 1; n <= M; ++n) {
+        for (int q = 0; q < Q; ++q) {
+            o[q] = cfmaf(h[q][n], cadd(w[M + q - n], w[M + q + n]), o[q]);
+            asm volatile("" : "+v"(o[q].x), "+v"(o[q].y));
+        }
+    };
+    if constexpr (E == 1) tap(1);
+    if (NS > 0) beside(0);
 #pragma unroll
-        for (int q = 0; q < Q; ++q) o[q] = cfmaf(h[q][n], cadd(w[M + q - n], w[M + q + n]), o[q]);
+    for (int s = 1; s <= NS; ++s) {
+        __builtin_amdgcn_sched_barrier(0);
+        stage(s + kStagesAhead);
+        const int n = E + 2 * s - 1;
+        tap(n);
+        if (n + 1 <= M) tap(n + 1);
+        if (s < NS) beside(s);
     }
 }
 
-// Per-workgroup constants: frequencies per workgroup and sub-group size.
-__device__ __forceinline__ void group_shape(const SecDev& S, int kind, int& G, int& tsub)
+// Taps 2 i and 2 i + 1 of a table row.
+template <int M>
+__device__ __forceinline__ void load_pair(float2 (&h)[M + 1], const float2* row, int i)
 {
-    const int q = kind == 1 ? 2 : (kind == 2 ? 4 : 3);  // outputs per thread
-    tsub = ((S.nx + q - 1) / q + 63) / 64 * 64;
-    G = S.G;
+    const v4f v = tap_pair(row, 2 * i, 2 * i + 1 <= M);
+    h[2 * i] = make_float2(v.x, v.y);
+    if (2 * i + 1 <= M) h[2 * i + 1] = make_float2(v.z, v.w);
 }
 
 // slow[k][x] = slowness_of(vel[k][min(x, nx-1)]) for x < ldp, every section,
@@ -154,54 +174,104 @@ __global__ void k_slowness(BatchArgs a, int dist)
     }
 }
 
-struct Lane {
-    int t, x0, LB, r;
-    bool live, ok0, ok1;
-    double ar;
+// Refills.  Where some output of a wave changes, taps are loaded for all its outputs,
+// between the stages of the FIR: a load of 16 bytes per lane keeps the data path of the L1
+// busy for 16 clocks however many lanes ask and wherever the rows are cached, and a wave
+// waits until its loads are accepted.  As one masked block before the FIR they took 155 of
+// 575 us at 1024 points, 512 depths, 200 frequencies, layered, and 165 of 420 us at 601
+// points, 301 depths, 97 frequencies where every point changes at every step (now 514 and
+// 335 in all).
+template <int Q>
+struct Refill {
+    bool any;  // some output of the wave changes
+    int j[Q];  // its outputs' entries, where any
+    __device__ __forceinline__ void look_up(const BatchArgs& a, double ar, const double (&v)[Q])
+    {
+        bool chg = false;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) chg = chg || slowness_changed(v[q]);
+        any = __builtin_amdgcn_ballot_w64(chg) != 0;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) j[q] = 0;
+        if (any)
+#pragma unroll
+            for (int q = 0; q < Q; ++q) j[q] = index_of_slowness(ar, a.b, a.nk, slowness_value(v[q]));
+    }
 };
 
-// One depth step k with the current tap set.  All vector-memory operations
-// are issued first: the partial row of step k-1, refills of the other set for
-// step k+1 where the slowness changed, and the slowness prefetch for step
-// k+2; then the FIR.  The single wait at the top of the next step therefore
-// only covers operations issued a whole step earlier.
-template <int M, bool ROWS>
-__device__ __forceinline__ void step_fast(const BatchArgs& a, const SecDev& S, float2* sm,
-                                          const Lane& L, int k, float2 (&hc)[2][M + 1],
-                                          float2 (&ho)[2][M + 1], double2& sn, float2& o0,
-                                          float2& o1)
+// Slowness of Q outputs.
+template <int Q>
+__device__ __forceinline__ void load_slowness(const double* p, double (&v)[Q])
 {
-    wait_vmem_all();
-    if (ROWS && k >= 1) {
-        float* pr = L.live ? S.part + ((size_t)(k - 1) * S.nw + L.r) * S.ldp + L.x0
-                           : a.trash + L.x0;
-        store_partial2(pr, o0.x, o1.x);
+    if constexpr (Q % 2 == 0) {
+#pragma unroll
+        for (int q = 0; q < Q; q += 2) {
+            const double2 d = load_global(reinterpret_cast<const double2*>(p + q));
+            v[q] = d.x;
+            v[q + 1] = d.y;
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) v[q] = *as_global(p + q);
     }
-    // sn = slowness of step k+1, flagged where it differs from step k-1 (the
-    // step the other set was last loaded for)
-    if (k >= 1 && k + 1 < S.nsteps) {
-        if (slowness_changed(sn.x))
-            load_taps<M>(ho[0], a.tab + (size_t)index_of_slowness(L.ar, a.b, a.nk,
-                                                                  slowness_value(sn.x)) * (M + 1));
-        if (slowness_changed(sn.y))
-            load_taps<M>(ho[1], a.tab + (size_t)index_of_slowness(L.ar, a.b, a.nk,
-                                                                  slowness_value(sn.y)) * (M + 1));
-    }
-    const int kp = k + 2 < S.nsteps ? k + 2 : S.nsteps - 1;
-    const double2 p = load_global(reinterpret_cast<const double2*>(S.slow + (size_t)kp * S.ldp + L.x0));
-    fir2<M>(sm + (k & 1) * L.LB + 2 * L.t, hc[0], hc[1], o0, o1);
-    float2* dst = sm + ((k + 1) & 1) * L.LB + M + L.x0;
-    if (L.ok0) dst[0] = o0;
-    if (L.ok1) dst[1] = o1;
-    sn = p;
-    __syncthreads();
-    if (ROWS && publishes_at(k)) publish_block(a, S, k / kPublish - 1);
 }
 
-// Register-tap kernel, two outputs per thread.  Sub-group of tsub threads per
-// frequency; LDS per sub-group = two planes of 2*tsub + 2M + 2 points, P[x] at
-// offset M + x, zero elsewhere (the zero boundary of Eq. 1).
-template <int M, bool ROWS>
+// Write-through store of one partial-row value (see store_partial2).
+__device__ __forceinline__ void store_partial1(float* p, float a)
+{
+    __hip_atomic_store(as_global(p), a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <int M, int Q>
+struct FastLane {
+    int win;        // its window in the first plane
+    int plane;      // points of a plane
+    int out[2][Q];  // its outputs in either plane; past the section: a point that no one reads
+    int x0;
+    double ar;
+    size_t row;     // floats between partial rows (none where the frequency is not the section's)
+};
+
+// One depth step k with the current tap set: from plane PL to the other.  sp: the
+// slowness of step k+2, pr: the partial row of step k.
+template <int M, int Q, bool ROWS, int PL>
+__device__ __forceinline__ void step_fast(const BatchArgs& a, float2* sm, const FastLane<M, Q>& L,
+                                          const double* sp, float*& pr, bool publishes,
+                                          float2 (&hc)[Q][M + 1], float2 (&ho)[Q][M + 1],
+                                          double (&sn)[Q], float2 (&o)[Q])
+{
+    Refill<Q> next;
+    next.look_up(a, L.ar, sn);
+    load_slowness<Q>(sp + L.x0, sn);
+    const float2* row[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) row[q] = a.tab + (size_t)next.j[q] * (M + 1);
+    const auto refill = [&](int s) {
+        if (s % kRefillStages != 0 || !next.any) return;
+#pragma unroll
+        for (int i = s; i < s + kRefillStages && 2 * i <= M; ++i)
+#pragma unroll
+            for (int q = 0; q < Q; ++q) load_pair<M>(ho[q], row[q], i);
+    };
+    firq<M, Q>(sm + L.win + PL * L.plane, hc, o, refill);
+    refill(kStages<M, Q>);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) sm[L.out[1 - PL][q]] = o[q];
+    if (ROWS) {
+        if (publishes) wait_vmem_all();
+        if constexpr (Q == 2) store_partial2(pr, o[0].x, o[1].x);
+        else store_partial1(pr, o[0].x);
+        pr += L.row;
+    }
+    __syncthreads();
+}
+
+// Register-tap kernel, one or two outputs per thread.  Sub-group of tsub threads per
+// frequency; LDS per sub-group = two planes of Q*tsub + 2M + 2 points, P[x] at
+// offset M + x, zero elsewhere (the zero boundary of Eq. 1).  A step has no branch but
+// those of the refills and of publishing: with fewer than two waves per SIMD every
+// instruction costs 5 clocks.
+template <int M, int Q, bool ROWS>
 __global__ void __launch_bounds__(512) k_extrap_fast(BatchArgs a)
 {
     extern __shared__ float4 smem4[];
@@ -211,66 +281,75 @@ __global__ void __launch_bounds__(512) k_extrap_fast(BatchArgs a)
     }
     const ItemDev it = item_of(a, blockIdx.x - (ROWS ? a.nred : 0));
     const SecDev S = sec_of(a, it.sec);
-    int G, tsub;
-    group_shape(S, 1, G, tsub);
+    const int tsub = ((S.nx + Q - 1) / Q + 63) / 64 * 64, G = S.G;
     const int g = threadIdx.x / tsub;
-    Lane L;
-    L.LB = 2 * tsub + 2 * M + 2;
+    const int LB = Q * tsub + 2 * M + 2;
     if (g >= G) {
         idle_barriers(2 + S.nsteps + (ROWS ? 1 : 0));
         return;
     }
-    float2* sm = reinterpret_cast<float2*>(smem4) + (size_t)g * 2 * L.LB;
-    L.t = threadIdx.x - g * tsub;
-    L.live = it.r0 + g < S.nw;
-    L.r = L.live ? it.r0 + g : S.nw - 1;
-    L.x0 = 2 * L.t;
-    L.ok0 = L.live && L.x0 < S.nx;
-    L.ok1 = L.live && L.x0 + 1 < S.nx;
-    L.ar = S.omega[L.r] / a.dk;
-
-    for (int i = L.t; i < 2 * L.LB; i += tsub) sm[i] = make_float2(0.0f, 0.0f);
-    __syncthreads();
-    if (L.ok0) sm[M + L.x0] = S.win[(size_t)L.x0 * S.nw + L.r];
-    if (L.ok1) sm[M + L.x0 + 1] = S.win[(size_t)(L.x0 + 1) * S.nw + L.r];
-
-    float2 hA[2][M + 1], hB[2][M + 1];
-    {
-        const double2 s0 = *reinterpret_cast<const double2*>(S.slow + L.x0);
-        load_taps<M>(hA[0], a.tab + (size_t)index_of_slowness(L.ar, a.b, a.nk, slowness_value(s0.x)) * (M + 1));
-        load_taps<M>(hA[1], a.tab + (size_t)index_of_slowness(L.ar, a.b, a.nk, slowness_value(s0.y)) * (M + 1));
-        const int k1 = S.nsteps > 1 ? 1 : 0;
-        const double2 s1 = *reinterpret_cast<const double2*>(S.slow + (size_t)k1 * S.ldp + L.x0);
-        load_taps<M>(hB[0], a.tab + (size_t)index_of_slowness(L.ar, a.b, a.nk, slowness_value(s1.x)) * (M + 1));
-        load_taps<M>(hB[1], a.tab + (size_t)index_of_slowness(L.ar, a.b, a.nk, slowness_value(s1.y)) * (M + 1));
+    float2* const sm = reinterpret_cast<float2*>(smem4);
+    const int t = threadIdx.x - g * tsub;
+    const bool live = it.r0 + g < S.nw;
+    const int r = live ? it.r0 + g : S.nw - 1;
+    const int base = g * 2 * LB;
+    FastLane<M, Q> L;
+    L.x0 = Q * t;
+    L.win = base + Q * t;
+    L.plane = LB;
+    bool ok[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        ok[q] = live && L.x0 + q < S.nx;
+        for (int pl = 0; pl < 2; ++pl)
+            L.out[pl][q] = ok[q] ? base + pl * LB + M + L.x0 + q : G * 2 * LB;
     }
-    double2 sn = make_double2(0.0, 0.0);
+    L.ar = S.omega[r] / a.dk;
+    L.row = live ? (size_t)S.nw * S.ldp : 0;
+
+    for (int i = t; i < 2 * LB; i += tsub) sm[base + i] = make_float2(0.0f, 0.0f);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+        if (ok[q]) sm[base + M + L.x0 + q] = S.win[(size_t)(L.x0 + q) * S.nw + r];
+
+    float2 hA[Q][M + 1], hB[Q][M + 1];
+    {
+        double v[Q];
+        load_slowness<Q>(S.slow + L.x0, v);
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            load_taps<M>(hA[q], a.tab + (size_t)index_of_slowness(L.ar, a.b, a.nk, slowness_value(v[q])) * (M + 1));
+        load_slowness<Q>(S.slow + (size_t)(S.nsteps > 1 ? 1 : 0) * S.ldp + L.x0, v);
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            load_taps<M>(hB[q], a.tab + (size_t)index_of_slowness(L.ar, a.b, a.nk, slowness_value(v[q])) * (M + 1));
+    }
+    double sn[Q] = {};  // slowness of the step after, flagged where the other set is to be refilled
+    const double* sp = S.slow + (size_t)(S.nsteps > 2 ? 2 : S.nsteps - 1) * S.ldp;
+    float* pr = live ? S.part + (size_t)r * S.ldp + L.x0 : a.trash + L.x0;
     __syncthreads();
 
-    float2 o0 = make_float2(0.0f, 0.0f), o1 = o0;
+    float2 o[Q] = {};
     for (int k = 0; k < S.nsteps; k += 2) {
-        step_fast<M, ROWS>(a, S, sm, L, k, hA, hB, sn, o0, o1);
+        step_fast<M, Q, ROWS, 0>(a, sm, L, sp, pr, false, hA, hB, sn, o);
         if (k + 1 >= S.nsteps) break;
-        step_fast<M, ROWS>(a, S, sm, L, k + 1, hB, hA, sn, o0, o1);
+        sp += k + 3 < S.nsteps ? S.ldp : 0;
+        const bool publishes = ROWS && publishes_at(k + 1);
+        step_fast<M, Q, ROWS, 1>(a, sm, L, sp, pr, publishes, hB, hA, sn, o);
+        sp += k + 4 < S.nsteps ? S.ldp : 0;
+        if (publishes) publish_block(a, S, (k + 1) / kPublish - 1);
     }
     if (ROWS) {
-        float* pr = L.live ? S.part + ((size_t)(S.nsteps - 1) * S.nw + L.r) * S.ldp + L.x0
-                           : a.trash + L.x0;
-        store_partial2(pr, o0.x, o1.x);
         wait_vmem_all();
         __syncthreads();
         for (int b = published_in_loop(S.nsteps); b * kPublish < S.nsteps; ++b) publish_block(a, S, b);
     }
     if (S.wout) {
-        if (L.ok0) S.wout[(size_t)L.x0 * S.nw + L.r] = o0;
-        if (L.ok1) S.wout[(size_t)(L.x0 + 1) * S.nw + L.r] = o1;
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (ok[q]) S.wout[(size_t)(L.x0 + q) * S.nw + r] = o[q];
     }
-}
-
-// Write-through store of one partial-row value (see store_partial2).
-__device__ __forceinline__ void store_partial1(float* p, float a)
-{
-    __hip_atomic_store(as_global(p), a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Partial row of Q outputs.  Q = 4: x0 is a multiple of 4 and 4 * tsub is
@@ -291,13 +370,14 @@ __device__ __forceinline__ void store_partial_q(float* pr, const float2 (&o)[Q],
 }
 
 // Register-tap kernel for wider sections (nx <= Q * 512): Q = 3 or 4 outputs
-// per thread and one tap set (two do not fit in 256 VGPRs), refilled at the
-// end of a step for outputs whose slowness changes at the next step.  A
-// workgroup touches only the table rows of its own frequency, so refills
-// mostly hit in L1 and the barrier covers part of their latency.  One
-// frequency per workgroup.  Q = 3 serves 1024 < nx <= 1536: there Q = 4 would
-// leave 5 or 6 waves for 4 SIMDs (the SIMD with two waves sets the pace),
-// while Q = 3 gives 6 to 8 waves and three quarters of the work per wave.
+// per thread and one tap set (two do not fit in 256 VGPRs), whose taps are
+// replaced as the FIR has used them for the last time, where the slowness of some
+// output of the wave changes at the next step.  One frequency per workgroup.  Q = 3
+// serves 1024 < nx <= 1536: there Q = 4 would leave 5 or 6 waves for 4 SIMDs (the
+// SIMD with two waves sets the pace), while Q = 3 gives 6 to 8 waves and three
+// quarters of the work per wave.  Bound by the FP32 instruction rate and, where
+// waves refill, by the L1's data path.  1501 points, 300 depths, 101 frequencies:
+// layered 587 -> 541 us, a velocity that varies from point to point 782 -> 705 us.
 template <int M, int Q, bool ROWS>
 __global__ void __launch_bounds__(512) k_extrap_wide(BatchArgs a)
 {
@@ -308,8 +388,7 @@ __global__ void __launch_bounds__(512) k_extrap_wide(BatchArgs a)
     }
     const ItemDev it = item_of(a, blockIdx.x - (ROWS ? a.nred : 0));
     const SecDev S = sec_of(a, it.sec);
-    int G, tsub;
-    group_shape(S, Q == 4 ? 2 : 3, G, tsub);
+    const int tsub = ((S.nx + Q - 1) / Q + 63) / 64 * 64;
     if ((int)threadIdx.x >= tsub) {
         idle_barriers(2 + S.nsteps + (ROWS ? 1 : 0));
         return;
@@ -341,49 +420,55 @@ __global__ void __launch_bounds__(512) k_extrap_wide(BatchArgs a)
         load_taps<M>(h[q], a.tab + (size_t)index_of_slowness(ar, a.b, a.nk, slowness_value(S.slow[xs[q]])) * (M + 1));
     __syncthreads();
 
+    const auto slowness = [&](int k, double (&v)[Q]) {  // flagged where it differs from row k-1
+        const double* sp = S.slow + (size_t)(k < S.nsteps ? k : S.nsteps - 1) * S.ldp;
+        if constexpr (Q == 4) load_slowness<Q>(sp + x0, v);
+        else
+#pragma unroll
+            for (int q = 0; q < Q; ++q) v[q] = *as_global(sp + xs[q]);
+    };
+    double sn[Q];
+    slowness(1, sn);
+    float* pr = live ? S.part + (size_t)r * S.ldp + x0 : a.trash + x0;
+    const size_t row = live ? (size_t)S.nw * S.ldp : 0;
+
     float2 o[Q];
-#pragma unroll
-    for (int q = 0; q < Q; ++q) o[q] = make_float2(0.0f, 0.0f);
     for (int k = 0; k < S.nsteps; ++k) {
-        wait_vmem_all();
-        if (ROWS && k >= 1) {
-            float* pr = live ? S.part + ((size_t)(k - 1) * S.nw + r) * S.ldp + x0 : a.trash + x0;
-            store_partial_q<Q>(pr, o, ok);
-        }
-        // slowness of step k+1 (flagged where it differs from step k), used
-        // after the FIR to refill taps
-        const int kp = k + 1 < S.nsteps ? k + 1 : S.nsteps - 1;
-        const double* sp = S.slow + (size_t)kp * S.ldp;
-        double sn[Q];
-        if constexpr (Q == 4) {
-            const double2 p01 = load_global(reinterpret_cast<const double2*>(sp + x0));
-            const double2 p23 = load_global(reinterpret_cast<const double2*>(sp + x0 + 2));
-            sn[0] = p01.x;
-            sn[1] = p01.y;
-            sn[2] = p23.x;
-            sn[3] = p23.y;
-        } else {
+        Refill<Q> next;
+        next.look_up(a, ar, sn);
+        slowness(k + 2, sn);
+        // after stage s: the pairs of taps that it and the stages before were the last to use
+        constexpr int NS = kStages<M, Q>;
+        const auto refill = [&](int s) {
+            if ((s % kRefillStages != kRefillStages - 1 && s != NS) || !next.any) return;
+            const auto group = [](int i) {
+                const int last = 2 * i + 1 <= kCentre<M, Q> ? 0 : (2 * i + 2 - kCentre<M, Q>) / 2;
+                const int g = last / kRefillStages * kRefillStages + kRefillStages - 1;
+                return g < NS ? g : NS;
+            };
 #pragma unroll
-            for (int q = 0; q < Q; ++q) sn[q] = *as_global(sp + xs[q]);
-        }
-        firq<M, Q>(sm + (k & 1) * LB + x0, h, o);
+            for (int q = 0; q < Q; ++q) {
+                const float2* row = a.tab + (size_t)next.j[q] * (M + 1);
+#pragma unroll
+                for (int i = 0; 2 * i <= M; ++i)
+                    if (group(i) == s) load_pair<M>(h[q], row, i);
+            }
+        };
+        firq<M, Q>(sm + (k & 1) * LB + x0, h, o, refill);
         float2* dst = sm + ((k + 1) & 1) * LB + M + x0;
 #pragma unroll
         for (int q = 0; q < Q; ++q)
             if (ok[q]) dst[q] = o[q];
-        if (k + 1 < S.nsteps) {
-#pragma unroll
-            for (int q = 0; q < Q; ++q)
-                if (slowness_changed(sn[q]))
-                    load_taps<M>(h[q], a.tab + (size_t)index_of_slowness(ar, a.b, a.nk,
-                                                                         slowness_value(sn[q])) * (M + 1));
+        refill(NS);
+        if (ROWS) {
+            if (publishes_at(k)) wait_vmem_all();
+            store_partial_q<Q>(pr, o, ok);
+            pr += row;
         }
         __syncthreads();
         if (ROWS && publishes_at(k)) publish_block(a, S, k / kPublish - 1);
     }
     if (ROWS) {
-        float* pr = live ? S.part + ((size_t)(S.nsteps - 1) * S.nw + r) * S.ldp + x0 : a.trash + x0;
-        store_partial_q<Q>(pr, o, ok);
         wait_vmem_all();
         __syncthreads();
         for (int b = published_in_loop(S.nsteps); b * kPublish < S.nsteps; ++b) publish_block(a, S, b);
@@ -465,15 +550,27 @@ __global__ void __launch_bounds__(64) k_rows(const float* __restrict__ part,
         if (x + q < nx) row[q] = acc[q];
 }
 
+template <int M, int Q>
+int launch_fast_as(const BatchArgs& a, int threads, size_t lds, hipStream_t s)
+{
+    if (a.rows)
+        hipLaunchKernelGGL((k_extrap_fast<M, Q, true>), dim3(a.nitems + a.nred), dim3(threads), lds,
+                           s, a);
+    else
+        hipLaunchKernelGGL((k_extrap_fast<M, Q, false>), dim3(a.nitems), dim3(threads), lds, s, a);
+    return hipGetLastError() == hipSuccess ? MIG_OK : MIG_E_DEVICE;
+}
+
 template <int M>
 int launch_fast(const BatchArgs& a, int threads, size_t lds, hipStream_t s)
 {
-    if (a.rows)
-        hipLaunchKernelGGL((k_extrap_fast<M, true>), dim3(a.nitems + a.nred), dim3(threads), lds,
-                           s, a);
-    else
-        hipLaunchKernelGGL((k_extrap_fast<M, false>), dim3(a.nitems), dim3(threads), lds, s, a);
-    return hipGetLastError() == hipSuccess ? MIG_OK : MIG_E_DEVICE;
+    return launch_fast_as<M, 2>(a, threads, lds, s);
+}
+
+template <int M>
+int launch_narrow(const BatchArgs& a, int threads, size_t lds, hipStream_t s)
+{
+    return launch_fast_as<M, 1>(a, threads, lds, s);
 }
 
 template <int M, int Q>
@@ -507,6 +604,7 @@ typedef int (*launch_fn)(const BatchArgs&, int, size_t, hipStream_t);
     {&f<0>, &f<1>, &f<2>, &f<3>, &f<4>, &f<5>, &f<6>, &f<7>, &f<8>, &f<9>, &f<10>,     \
      &f<11>, &f<12>, &f<13>, &f<14>, &f<15>, &f<16>, &f<17>}
 const launch_fn kFast[] = MIG_INST(launch_fast);
+const launch_fn kNarrow[] = MIG_INST(launch_narrow);
 const launch_fn kWide[] = MIG_INST(launch_wide4);
 const launch_fn kMid[] = MIG_INST(launch_wide3);
 constexpr int kRegMaxM = 17;
@@ -525,6 +623,19 @@ int extrap_kernel_kind(int nx, int M)
     return 0;
 }
 
+// One output per thread instead of two: twice the waves, half the chain of each, but
+// windows of 8-byte LDS reads (twice the LDS clocks per output).  Up to 256 points (four
+// waves, one per SIMD) always: 300 depths, 150 frequencies, 35 taps, layered, 200 points:
+// 257 -> 182 us, 290 frequencies: 270 -> 216 us.  Up to 512 points (eight waves) where
+// every workgroup has a CU to itself: 150 frequencies, 400 points: 261 -> 235 us, 512
+// points: 264 -> 242 us, but 290 frequencies of 450 points: 329 -> 374 us.
+bool extrap_narrow(int kind, int nx, int G, int nitems, int cus)
+{
+    return kind == 1 && G * ((nx + 63) / 64 * 64) <= 512 && (nx <= 256 || nitems <= cus);
+}
+
+int threads_narrow(int nx) { return (nx + 63) / 64 * 64; }
+
 int threads_per_omega(int kind, int nx)
 {
     if (kind == 1) return ((nx + 1) / 2 + 63) / 64 * 64;
@@ -542,12 +653,13 @@ int launch_slowness(const BatchArgs& a, int max_rows, int max_ldp, int dist, hip
     return hipGetLastError() == hipSuccess ? MIG_OK : MIG_E_DEVICE;
 }
 
-int launch_extrap(const BatchArgs& a, int kind, int threads, hipStream_t s)
+int launch_extrap(const BatchArgs& a, int kind, int threads, bool narrow, hipStream_t s)
 {
     // LDS: G sub-groups x two planes; the host picks threads = G * tsub.
     if (kind == 1) {
-        int tsub_min = 64;
-        size_t lds = (size_t)2 * (2 * threads + (threads / tsub_min) * (2 * a.M + 2)) * sizeof(float2);
+        const int Q = narrow ? 1 : 2;
+        const size_t lds = (size_t)2 * (Q * threads + threads / 64 * (2 * a.M + 2) + 1) * sizeof(float2);
+        if (Q == 1) return kNarrow[a.M](a, threads, lds, s);
         return kFast[a.M](a, threads, lds, s);
     }
     if (kind == 2 || kind == 3) {

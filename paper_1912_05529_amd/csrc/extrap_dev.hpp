@@ -78,12 +78,12 @@ __device__ __forceinline__ void publish_block(const BatchArgs& a, const SecDev& 
     }
 }
 
-// Block b (steps 32b .. 32b+31) is published at the end of step 32b+33: its
-// last partial row was stored at the start of step 32b+32, the wait for all
-// memory operations at the start of step 32b+33 covers it, and the barrier
-// ending that step means every wave of the workgroup has passed that wait.
-// So no extra wait stands in the loop.  Blocks whose publishing step lies
-// past the last step are published after the loop.
+// Block b (steps 32b .. 32b+31) is published at the end of step 32b+33.  Its last partial
+// row is stored at the latest at the start of step 32b+32; in step 32b+33 every wave
+// waits for its memory operations before it stores that step's row, and the barrier that
+// ends the step means every wave of the workgroup has passed that wait, which by then
+// finds the stores complete.  Blocks whose publishing step lies past the last step are
+// published after the loop.
 __device__ __forceinline__ bool publishes_at(int k) { return k >= kPublish + 1 && k % kPublish == 1; }
 __device__ __forceinline__ int published_in_loop(int nsteps)
 {
