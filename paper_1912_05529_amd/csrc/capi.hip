@@ -95,8 +95,10 @@ int reducer_count(int nprod, int want)
     return n < cap ? n : cap;
 }
 
-// Idle CUs from which on image rows are formed beside the depth stepping.
+// Image rows are formed beside the depth stepping where it leaves this many CUs idle ...
 constexpr int kReducerCus = 32;
+// ... and the partial rows are more than this (kinds 1 and 3; see run_extrap).
+constexpr size_t kRowsAfter = (size_t)64 << 20;
 
 int blocks_of(int nsteps) { return (nsteps + kPublish - 1) / kPublish; }
 
@@ -247,7 +249,16 @@ int run_extrap(const float2* src, float2* dst, const float* vel, const double* o
         // for need not be written through: 845 against 977 us at 3001 points).
         const int nb = blocks_of(cs);
         a.rows = rows ? 1 : 0;
-        const bool beside = rows && nb > 1 && kind != 0 && (tn.nred > 0 || device_cus() - nitems >= kReducerCus);
+        // Few partial rows are summed faster than reducers cost the frequency
+        // workgroups beside them: 128 points, 300 depths, 150 frequencies 187 -> 161 us
+        // without them, 300 points 204 -> 193 us, 1501 points, 100 depths, 100
+        // frequencies 210 -> 192 us; but 601 points, 301 depths, 97 frequencies (70 MB)
+        // 344 -> 353 us, 700 points, 512 depths, 200 frequencies 468 -> 495 us, and in
+        // kind 2 2000 points, 60 depths, 100 frequencies (48 MB) 130 -> 133 us.
+        const bool tuned = tn.nred > 0 || tn.stall_us > 0 || tn.flags != 0;
+        const bool few = kind != 2 && (size_t)cs * nw * nx * sizeof(float) <= kRowsAfter;
+        const bool beside = rows && nb > 1 && kind != 0 &&
+                            (tuned || (device_cus() - nitems >= kReducerCus && !few));
         if (beside) {
             const int nred = reducer_count(nitems, tn.nred);
             a.parts = parts_of(nx);
