@@ -235,6 +235,7 @@ int launch_clear_status(int* status, hipStream_t s);
 // ([step][nw][ldp] floats), after the depth-stepping launch.
 int launch_rows(const float* part, double* rows, int s0, int s1, int nx, int nw, int ldp,
                 hipStream_t s);
+int launch_rows_batch(const BatchArgs& a, int max_nx, int max_rows, hipStream_t s);
 
 // One 3-D depth step (device pointers; planes are [nw][nx][ny]).
 struct Step3dArgs {

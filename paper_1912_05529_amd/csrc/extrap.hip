@@ -519,14 +519,9 @@ __global__ void k_index(const float* __restrict__ vel, const double* __restrict_
 // every CU; 16 loads of 16 bytes in flight per thread (row strides are multiples of 256
 // points; the last thread of a row reads its padding, which frequency workgroups of
 // odd widths leave unwritten, and does not store those sums).
-__global__ void __launch_bounds__(64) k_rows(const float* __restrict__ part,
-                                             double* __restrict__ rows, int s0, int nx, int nw,
-                                             int ldp)
+__device__ __forceinline__ void sum_rows(const float* __restrict__ part, double* __restrict__ rows,
+                                         int st, int x, int nx, int nw, int ldp)
 {
-    typedef float v4f __attribute__((ext_vector_type(4)));
-    const int x = 4 * (blockIdx.x * blockDim.x + threadIdx.x);
-    if (x >= nx) return;
-    const int st = s0 + blockIdx.y;
     const float* p = part + (size_t)st * nw * ldp + x;
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     const auto add = [&](const v4f& v) {
@@ -548,6 +543,24 @@ __global__ void __launch_bounds__(64) k_rows(const float* __restrict__ part,
 #pragma unroll
     for (int q = 0; q < 4; ++q)
         if (x + q < nx) row[q] = acc[q];
+}
+
+// Steps s0 .. of one section: nbx workgroups per row.
+__global__ void __launch_bounds__(64) k_rows(const float* __restrict__ part,
+                                             double* __restrict__ rows, int s0, int nx, int nw,
+                                             int ldp, int nbx)
+{
+    const int x = 4 * (blockIdx.x % nbx * 64 + threadIdx.x);
+    if (x < nx) sum_rows(part, rows, s0 + blockIdx.x / nbx, x, nx, nw, ldp);
+}
+
+// Every step of every section of a batch: nbx workgroups per row, as many rows as the
+// longest section has.
+__global__ void __launch_bounds__(64) k_rows_batch(BatchArgs a, int nbx)
+{
+    const SecDev S = sec_of(a, blockIdx.y);
+    const int x = 4 * (blockIdx.x % nbx * 64 + threadIdx.x), st = blockIdx.x / nbx;
+    if (x < S.nx && st < S.nsteps) sum_rows(S.part, S.rows, st, x, S.nx, S.nw, S.ldp);
 }
 
 template <int M, int Q>
@@ -674,8 +687,17 @@ int launch_rows(const float* part, double* rows, int s0, int s1, int nx, int nw,
                 hipStream_t s)
 {
     if (s1 <= s0) return MIG_OK;
-    dim3 grid((nx + 255) / 256, s1 - s0);
-    hipLaunchKernelGGL(k_rows, grid, dim3(64), 0, s, part, rows, s0, nx, nw, ldp);
+    const int nbx = (nx + 255) / 256;
+    const dim3 grid((unsigned)nbx * (unsigned)(s1 - s0));
+    hipLaunchKernelGGL(k_rows, grid, dim3(64), 0, s, part, rows, s0, nx, nw, ldp, nbx);
+    return hipGetLastError() == hipSuccess ? MIG_OK : MIG_E_DEVICE;
+}
+
+int launch_rows_batch(const BatchArgs& a, int max_nx, int max_rows, hipStream_t s)
+{
+    const int nbx = (max_nx + 255) / 256;
+    const dim3 grid((unsigned)nbx * (unsigned)max_rows, a.nsec);
+    hipLaunchKernelGGL(k_rows_batch, grid, dim3(64), 0, s, a, nbx);
     return hipGetLastError() == hipSuccess ? MIG_OK : MIG_E_DEVICE;
 }
 

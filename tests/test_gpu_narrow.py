@@ -1,8 +1,9 @@
 """Depth stepping with one output per thread (up to 512 points) against two outputs per
 thread (the batched form): planes of both are the same sums in the same order, so images
-are the same bits.  And refills of every width against the FP64 oracle where every output
+are the same bits.  Refills of every width against the FP64 oracle where every output
 changes its filter at every step.  Tolerance: relative L2 1e-5 after a few steps (FP32
-taps and arithmetic: about 1e-7 per operation, 2 N operations per output and step)."""
+taps and arithmetic: about 1e-7 per operation, 2 N operations per output and step).  Batches whose
+image rows are summed after the launch."""
 import pytest
 import torch
 
@@ -42,3 +43,21 @@ def test_refills(nx, nw, nsteps, ntaps, layered):
                                              data64(sec), nsteps)
     assert rel_l2(plane.cpu().numpy(), ref_plane) <= 1e-5
     assert rel_l2(rows.cpu().numpy(), ref_rows) <= 1e-5
+
+
+@pytest.mark.parametrize("nxs,nw,nz,ntaps", [
+    ((300, 129, 512, 1000), 70, 40, 25), ((1100, 1501), 120, 5, 35), ((1600, 2048, 1537), 90, 4, 35),
+    ((2049, 100, 3000), 90, 3, 37), ((64,), 300, 3, 11), ((64, 65, 1024, 1200, 2000, 2100), 60, 35, 35)])
+def test_batch_rows_after_the_launch(nxs, nw, nz, ntaps):
+    """Batches with more workgroups than CUs (sections of unequal depths and frequencies):
+    the same bits as each section by itself."""
+    print("batch nx=%s N=%d" % (nxs, ntaps), flush=True)
+    secs = [synth.random_case(9500 + nx, nx, nz + i, nw + 3 * i, ntaps=ntaps, nk=128) for i, nx in enumerate(nxs)]
+    tab = mig.design_table(secs[0].desc, dev())["tab32"]
+    batch, want = [], []
+    for sec in secs:
+        t = upload(sec)
+        want.append(mig.migrate(t["data"], t["vel"], t["omega"], tab, secs[0].desc))
+        batch.append(dict(t, image=torch.full_like(want[-1], float("nan"))))
+    for got, ref in zip(mig.migrate_batched(batch, tab, secs[0].desc), want):
+        assert torch.equal(got, ref)
