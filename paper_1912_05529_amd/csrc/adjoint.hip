@@ -16,7 +16,7 @@
 //     change points): per step it forms g_m[y] = conj(h_{j(y)}[m]) q[y] for its
 //     points in LDS and gathers out[x] = g_0[x] + sum_m (g_m[x-m] + g_m[x+m]);
 //   * general (adjoint_long.hip): any size and velocity; runs where the other two do not.
-#include "common.hpp"
+#include "extrap_dev.hpp"
 
 namespace mig {
 namespace {
@@ -302,72 +302,6 @@ __device__ AdjChunk adj_lane_chunk(int lane, int M, int T)
     return c;
 }
 
-// Two outputs x0, x0+1 of the folded FIR with conjugated taps,
-// sum_n conj(h[n]) (w[M-n] + w[M+n]), from the window w[i] = P[x0 - M + i]
-// (16-byte LDS reads); the conjugation is a sign in the multiply-adds.  Two
-// passes (taps 0..P, then P+1..M), each reading only the window part it uses,
-// with a scheduling barrier between them: the whole window would take 72
-// registers next to the two tap sets.
-template <int M, int LO, int HI>
-__device__ __forceinline__ void fold2_pass(const float4* __restrict__ w4, const float2 (&h0)[M + 1],
-                                           const float2 (&h1)[M + 1], float2& a0, float2& a1)
-{
-    // window indices this pass reads: out0 uses M-n, M+n; out1 M+1-n, M+1+n
-    constexpr int lo = M - HI, hi = M + 1 + HI;                 // outer bounds
-    constexpr int ilo = lo / 2, ihi = hi / 2;
-    float2 w[2 * M + 2];
-#pragma unroll
-    for (int i = ilo; i <= ihi; ++i) {
-        const bool inner_gap = LO > 0 && 2 * i > M - LO + 1 && 2 * i + 1 < M + LO;
-        if (inner_gap) continue;
-        // a native 4-float vector keeps the read one 16-byte LDS access (the
-        // HIP float4 struct is copied field by field, and 8-byte reads at a
-        // 16-byte lane stride conflict on the banks)
-        typedef float v4f __attribute__((ext_vector_type(4)));
-        const v4f q = *reinterpret_cast<const v4f*>(w4 + i);
-        w[2 * i] = make_float2(q.x, q.y);
-        w[2 * i + 1] = make_float2(q.z, q.w);
-    }
-#pragma unroll
-    for (int n = LO; n <= HI; ++n) {
-        if (n == 0) {
-            a0.x = fmaf(h0[0].x, w[M].x, a0.x);
-            a0.x = fmaf(h0[0].y, w[M].y, a0.x);
-            a0.y = fmaf(h0[0].x, w[M].y, a0.y);
-            a0.y = fmaf(-h0[0].y, w[M].x, a0.y);
-            a1.x = fmaf(h1[0].x, w[M + 1].x, a1.x);
-            a1.x = fmaf(h1[0].y, w[M + 1].y, a1.x);
-            a1.y = fmaf(h1[0].x, w[M + 1].y, a1.y);
-            a1.y = fmaf(-h1[0].y, w[M + 1].x, a1.y);
-            continue;
-        }
-        const float2 s0 = make_float2(w[M - n].x + w[M + n].x, w[M - n].y + w[M + n].y);
-        const float2 s1 = make_float2(w[M + 1 - n].x + w[M + 1 + n].x, w[M + 1 - n].y + w[M + 1 + n].y);
-        a0.x = fmaf(h0[n].x, s0.x, a0.x);
-        a0.x = fmaf(h0[n].y, s0.y, a0.x);
-        a0.y = fmaf(h0[n].x, s0.y, a0.y);
-        a0.y = fmaf(-h0[n].y, s0.x, a0.y);
-        a1.x = fmaf(h1[n].x, s1.x, a1.x);
-        a1.x = fmaf(h1[n].y, s1.y, a1.x);
-        a1.y = fmaf(h1[n].x, s1.y, a1.y);
-        a1.y = fmaf(-h1[n].y, s1.x, a1.y);
-    }
-}
-
-template <int M>
-__device__ __forceinline__ void fold2(const float2* __restrict__ win, const float2 (&h0)[M + 1],
-                                      const float2 (&h1)[M + 1], float2& o0, float2& o1)
-{
-    constexpr int P = M / 2;
-    const float4* w4 = reinterpret_cast<const float4*>(win);
-    float2 a0 = make_float2(0.0f, 0.0f), a1 = a0, b0 = a0, b1 = a0;  // a sum per pass: shorter chains
-    fold2_pass<M, 0, P>(w4, h0, h1, a0, a1);
-    __builtin_amdgcn_sched_barrier(0);
-    fold2_pass<M, P + 1, M>(w4, h0, h1, b0, b1);
-    o0 = make_float2(a0.x + b0.x, a0.y + b0.y);
-    o1 = make_float2(a1.x + b1.x, a1.y + b1.y);
-}
-
 // LDS of the folded kernel: two planes, a row of corrections per wave (its
 // 128 outputs), then per parity the differences D_c[1..M] of each change
 // point followed by a zero.
@@ -436,9 +370,10 @@ struct FoldCarry {
     int nb;                   // change count of the row after (uniform)
     int jp;                   // (left | right << 16) entries of its change point i_ld
     double2 img;              // image row
+    double2 sn;               // slowness of the row after, flagged where it differs from this row
 };
 
-template <int M>
+template <int M, int AHEAD>
 __device__ __forceinline__ void fold_step(const AdjArgs& a, float2* sm, float4* cw, float2* dh,
                                           const FoldState& F, const FoldLane<adj_chunk_len(M)>& CL,
                                           int k_in, float2 (&h)[2][M + 1], FoldCarry& C)
@@ -457,6 +392,28 @@ __device__ __forceinline__ void fold_step(const AdjArgs& a, float2* sm, float4* 
     const int n_build = C.nb;
     const int i_ld = F.i_ld, m_ld = F.m_ld;
     const bool build = k >= 1 && F.on && i_ld < n_build;
+    // taps of step k-1, where row k-1 differs from row k under some output of the wave:
+    // loaded for all its outputs as the FIR has used them for the last time (before: one
+    // masked block behind the FIR.  1501 points, 300 depths, 101 frequencies, layered:
+    // 752 -> 655 us; 1024 points, 512 depths, 200 frequencies: 791 us either way, there
+    // the waves with corrections set the pace)
+    const bool refills = k >= 1 && __builtin_amdgcn_ballot_w64(slowness_changed(C.sn.x) ||
+                                                               slowness_changed(C.sn.y)) != 0;
+    int j[2] = {0, 0};
+    if (refills) {
+        j[0] = index_of_slowness(F.ar, a.b, a.nk, slowness_value(C.sn.x));
+        j[1] = index_of_slowness(F.ar, a.b, a.nk, slowness_value(C.sn.y));
+    }
+    const auto refill = [&](int s) {
+        if ((s % kRefillStages != kRefillStages - 1 && s != kStages<M, 2>) || !refills) return;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const float2* row = a.tab + (size_t)j[q] * (M + 1);
+#pragma unroll
+            for (int i = 0; 2 * i <= M; ++i)
+                if (refill_stage<M, 2>(i) == s) load_pair<M>(h[q], row, i);
+        }
+    };
     const int LB = F.LB;
     const float2* Pin = sm + ((k + 1) & 1) * LB;
     float2* Pout = sm + (k & 1) * LB + M;
@@ -520,14 +477,14 @@ __device__ __forceinline__ void fold_step(const AdjArgs& a, float2* sm, float4* 
         hl = load_global(a.tab + (size_t)((unsigned)C.jp & 0xffffu) * (M + 1) + m_ld);
     }
     // loads for this step's end and the next step, branch-free (rows clamped;
-    // values past the top are unused): slowness row k-1 (flagged where it
-    // differs from row k) for the refill at the end of this step, image row
-    // k-1 and its change points, the change count and entries of row k-2
+    // values past the top are unused): image row k-1 and its change points,
+    // the change count and entries of row k-2 and its slowness (flagged where
+    // it differs from row k-1) for the refills of the next step
     double2 sn, img_n;
     int cnt_n, mp_n, jp_n;
     {
         const int ks = k >= 1 ? k - 1 : 0, kn = k >= 2 ? k - 2 : 0;
-        sn = load_global(reinterpret_cast<const double2*>(a.slow + (size_t)ks * a.ldp + F.x0));
+        sn = load_global(reinterpret_cast<const double2*>(a.slow + (size_t)kn * a.ldp + F.x0));
         img_n = make_double2(a.image[(size_t)ks * nx + F.c0], a.image[(size_t)ks * nx + F.c1]);
         // vector loads: as scalar loads their completion would be tracked by
         // the counter the FIR's LDS waits use, and they would wait for them
@@ -541,8 +498,9 @@ __device__ __forceinline__ void fold_step(const AdjArgs& a, float2* sm, float4* 
     // own-filter FIR on Q_{k+1} (plane (k+1)&1), plus the image row and the
     // corrections (read back and cleared: LDS keeps one wave's accesses in
     // order, the fence keeps the compiler from moving the read up)
-    float2 o0, o1;
-    fold2<M>(Pin + F.x0, h[0], h[1], o0, o1);
+    float2 o[2];
+    firq<M, 2, true, AHEAD>(Pin + F.x0, h, o, refill);
+    float2 o0 = o[0], o1 = o[1];
     o0.x += (float)cimg.x;
     o1.x += (float)cimg.y;
     if (mask0) {
@@ -564,10 +522,11 @@ __device__ __forceinline__ void fold_step(const AdjArgs& a, float2* sm, float4* 
         C.mask = __ballot(rel);
         const int c = __builtin_amdgcn_readfirstlane(cnt_n);
         C.nb = c < a.kmax ? c : a.kmax;
-        asm volatile("" : "+v"(mp_n), "+v"(jp_n), "+v"(img_n.x), "+v"(img_n.y));
+        asm volatile("" : "+v"(mp_n), "+v"(jp_n), "+v"(img_n.x), "+v"(img_n.y), "+v"(sn.x), "+v"(sn.y));
         C.mp = mp_n;
         C.jp = jp_n;
         C.img = img_n;
+        C.sn = sn;
     }
     if (k >= 1) {
         // differences of row k-1 into the other cache (read from step k-1 on)
@@ -575,19 +534,15 @@ __device__ __forceinline__ void fold_step(const AdjArgs& a, float2* sm, float4* 
             const int kp = (k - 1) & 1;
             dh[(kp * kAdjKmax + i_ld) * (M + 1) + m_ld - 1] = make_float2(hr.x - hl.x, hr.y - hl.y);
         }
-        // taps of step k-1 where row k-1 differs from row k; the FIR of the
-        // next step waits for them (mostly L1 hits: the rows of one frequency)
-        if (slowness_changed(sn.x))
-            load_taps_adj<M>(h[0], a.tab + (size_t)index_of_slowness(F.ar, a.b, a.nk, slowness_value(sn.x)) * (M + 1));
-        if (slowness_changed(sn.y))
-            load_taps_adj<M>(h[1], a.tab + (size_t)index_of_slowness(F.ar, a.b, a.nk, slowness_value(sn.y)) * (M + 1));
     }
+    refill(kStages<M, 2>);
     __syncthreads();
 }
 
 // Up to 512 threads (1024 points), or 768: three waves per SIMD within 168 registers (up
-// to 1536 points; a fourth would spill).  1501 points, 101 frequencies, 300 depths, 35
-// taps, layered: 3630 -> 752 us (before: the general kernel, now 982 there).
+// to 1536 points; a fourth would spill; windows are read one stage ahead there, for
+// registers).  1501 points, 101 frequencies, 300 depths, 35 taps, layered: 3610 -> 655 us
+// (before: the general kernel, now 982 there).
 constexpr int kFoldMaxThreads = 768;
 
 template <int M, int THREADS>
@@ -654,9 +609,10 @@ __global__ void __launch_bounds__(THREADS) k_demigrate_fold(AdjArgs a)
         load_taps_adj<M>(h[1], a.tab + (size_t)index_of_slowness(F.ar, a.b, a.nk, slowness_value(s0.y)) * (M + 1));
     }
     C.img = make_double2(a.image[(size_t)k * nx + F.c0], a.image[(size_t)k * nx + F.c1]);
+    C.sn = *reinterpret_cast<const double2*>(a.slow + (size_t)(k >= 1 ? k - 1 : 0) * a.ldp + F.x0);
     __syncthreads();
 
-    for (; k >= 0; --k) fold_step<M>(a, sm, cw, dh, F, CL, k, h, C);
+    for (; k >= 0; --k) fold_step<M, THREADS <= 512 ? kStagesAhead : 1>(a, sm, cw, dh, F, CL, k, h, C);
     const float2* P0 = sm + M;  // Q_0 is in plane 0
     if (F.ok0) a.out[(size_t)F.x0 * a.nw + r] = P0[F.x0];
     if (F.ok1) a.out[(size_t)(F.x0 + 1) * a.nw + r] = P0[F.x0 + 1];

@@ -52,88 +52,6 @@ __device__ __forceinline__ void load_taps(float2 (&h)[M + 1], const float2* __re
     for (int n = 0; n <= M; ++n) h[n] = row[n];
 }
 
-// Stages of the FIR between two groups of tap refills (a branch each: one group per stage
-// costs waves that refill nothing 3 %; a FIR of its own for waves that refill makes the
-// compiler move whole tap sets where the two meet).
-constexpr int kRefillStages = 3;
-
-// Q adjacent outputs x0..x0+Q-1 from the window w[i] = P[x0 - M + i], i = 0..2M+Q-1.
-// Even Q: x0 is even, so the window is read with 16-byte LDS loads; odd Q (x0 of either
-// parity): 8-byte loads.  Points are read from the centre outwards, as the taps use them
-// (two taps per stage), kStagesAhead stages before their use: after a barrier every wave
-// of the CU reads at once, and a wave that asked for its whole window first would leave
-// the SIMDs idle until most of the CU's reads were done (1024 points, 300 depths, 150
-// frequencies, constant velocity: 280 -> 261 us).
-constexpr int kStagesAhead = 2;
-
-template <int M, int Q>
-constexpr int kCentre = Q % 2 == 0 && M % 2 ? 1 : 0;  // last tap of stage 0
-template <int M, int Q>
-constexpr int kStages = (M - kCentre<M, Q> + 1) / 2;  // stages after stage 0
-
-template <int M, int Q, class F>
-__device__ __forceinline__ void firq(const float2* __restrict__ win, const float2 (&h)[Q][M + 1],
-                                     float2 (&o)[Q], const F& beside)
-{
-    // Stage 0: points M - E .. M + Q - 1 + E, for taps 0 .. E.  Stage s: two points more on
-    // each side, for two taps more (the outermost may be cut short by the window's ends).
-    constexpr int E = kCentre<M, Q>, NS = kStages<M, Q>;
-    float2 w[2 * M + Q];
-    const auto load = [&](int i) {  // points i, i + 1 (i even where Q is)
-        if constexpr (Q % 2 == 0) {
-            const float4 q = *reinterpret_cast<const float4*>(win + i);
-            w[i] = make_float2(q.x, q.y);
-            w[i + 1] = make_float2(q.z, q.w);
-        } else {
-            if (i >= 0 && i < 2 * M + Q) w[i] = win[i];
-            if (i + 1 >= 0 && i + 1 < 2 * M + Q) w[i + 1] = win[i + 1];
-        }
-    };
-    const auto stage = [&](int s) {
-        if (s > NS) return;
-        load(M - E - 2 * s);
-        load(M + Q - 2 + E + 2 * s);
-    };
-#pragma unroll
-    for (int i = M - E; i < M + Q + E; i += 2) {
-        if (Q % 2 == 0 || i + 1 < M + Q) load(i);
-        else w[i] = win[i];
-    }
-#pragma unroll
-    for (int s = 1; s <= kStagesAhead; ++s) stage(s);
-#pragma unroll
-    for (int q = 0; q < Q; ++q) o[q] = cmulf(h[q][0], w[M + q]);
-    // (the outputs are pinned: left alone, the compiler sums one after the other and keeps
-    // the whole window in registers for it)
-    const auto tap = [&](int n) {
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            o[q] = cfmaf(h[q][n], cadd(w[M + q - n], w[M + q + n]), o[q]);
-            asm volatile("" : "+v"(o[q].x), "+v"(o[q].y));
-        }
-    };
-    if constexpr (E == 1) tap(1);
-    if (NS > 0) beside(0);
-#pragma unroll
-    for (int s = 1; s <= NS; ++s) {
-        __builtin_amdgcn_sched_barrier(0);
-        stage(s + kStagesAhead);
-        const int n = E + 2 * s - 1;
-        tap(n);
-        if (n + 1 <= M) tap(n + 1);
-        if (s < NS) beside(s);
-    }
-}
-
-// Taps 2 i and 2 i + 1 of a table row.
-template <int M>
-__device__ __forceinline__ void load_pair(float2 (&h)[M + 1], const float2* row, int i)
-{
-    const v4f v = tap_pair(row, 2 * i, 2 * i + 1 <= M);
-    h[2 * i] = make_float2(v.x, v.y);
-    if (2 * i + 1 <= M) h[2 * i + 1] = make_float2(v.z, v.w);
-}
-
 // slow[k][x] = slowness_of(vel[k][min(x, nx-1)]) for x < ldp, every section,
 // with the sign bit set where it differs (bitwise) from row k - dist (when
 // that row exists); also
@@ -441,17 +359,12 @@ __global__ void __launch_bounds__(512) k_extrap_wide(BatchArgs a)
         constexpr int NS = kStages<M, Q>;
         const auto refill = [&](int s) {
             if ((s % kRefillStages != kRefillStages - 1 && s != NS) || !next.any) return;
-            const auto group = [](int i) {
-                const int last = 2 * i + 1 <= kCentre<M, Q> ? 0 : (2 * i + 2 - kCentre<M, Q>) / 2;
-                const int g = last / kRefillStages * kRefillStages + kRefillStages - 1;
-                return g < NS ? g : NS;
-            };
 #pragma unroll
             for (int q = 0; q < Q; ++q) {
                 const float2* row = a.tab + (size_t)next.j[q] * (M + 1);
 #pragma unroll
                 for (int i = 0; 2 * i <= M; ++i)
-                    if (group(i) == s) load_pair<M>(h[q], row, i);
+                    if (refill_stage<M, Q>(i) == s) load_pair<M>(h[q], row, i);
             }
         };
         firq<M, Q>(sm + (k & 1) * LB + x0, h, o, refill);

@@ -28,6 +28,21 @@ __device__ __forceinline__ float2 cfmaf(float2 h, float2 s, float2 acc)
     return acc;
 }
 
+// the same with conj(h)
+__device__ __forceinline__ float2 cmulf_conj(float2 h, float2 u)
+{
+    return make_float2(fmaf(h.y, u.y, h.x * u.x), fmaf(-h.y, u.x, h.x * u.y));
+}
+
+__device__ __forceinline__ float2 cfmaf_conj(float2 h, float2 s, float2 acc)
+{
+    acc.x = fmaf(h.x, s.x, acc.x);
+    acc.x = fmaf(h.y, s.y, acc.x);
+    acc.y = fmaf(h.x, s.y, acc.y);
+    acc.y = fmaf(-h.y, s.x, acc.y);
+    return acc;
+}
+
 __device__ __forceinline__ float2 cadd(float2 a, float2 b)
 {
     return make_float2(a.x + b.x, a.y + b.y);
@@ -243,6 +258,106 @@ __device__ __forceinline__ v4f tap_pair(const float2* row, int n, bool two)
     if (two) return *(global_v4f)reinterpret_cast<const v4f_a8*>(row + n);
     const float2 a = load_global(row + n);
     return v4f{a.x, a.y, 0.0f, 0.0f};
+}
+
+// Stages of the FIR between two groups of tap refills (a branch each: one group per stage
+// costs waves that refill nothing 3 %; a FIR of its own for waves that refill makes the
+// compiler move whole tap sets where the two meet).
+constexpr int kRefillStages = 3;
+
+// Q adjacent outputs x0..x0+Q-1 from the window w[i] = P[x0 - M + i], i = 0..2M+Q-1.
+// Even Q: x0 is even, so the window is read with 16-byte LDS loads; odd Q (x0 of either
+// parity): 8-byte loads.  Points are read from the centre outwards, as the taps use them
+// (two taps per stage), kStagesAhead stages before their use: after a barrier every wave
+// of the CU reads at once, and a wave that asked for its whole window first would leave
+// the SIMDs idle until most of the CU's reads were done (1024 points, 300 depths, 150
+// frequencies, constant velocity: 280 -> 261 us).
+constexpr int kStagesAhead = 2;
+
+template <int M, int Q>
+constexpr int kCentre = Q % 2 == 0 && M % 2 ? 1 : 0;  // last tap of stage 0
+template <int M, int Q>
+constexpr int kStages = (M - kCentre<M, Q> + 1) / 2;  // stages after stage 0
+
+// CONJ: conjugated taps, and a sum each for even and odd taps (the adjoint; the forward
+// planes keep one sum in increasing order of taps).
+template <int M, int Q, bool CONJ = false, int AHEAD = kStagesAhead, class F>
+__device__ __forceinline__ void firq(const float2* __restrict__ win, const float2 (&h)[Q][M + 1],
+                                     float2 (&o)[Q], const F& beside)
+{
+    // Stage 0: points M - E .. M + Q - 1 + E, for taps 0 .. E.  Stage s: two points more on
+    // each side, for two taps more (the outermost may be cut short by the window's ends).
+    constexpr int E = kCentre<M, Q>, NS = kStages<M, Q>;
+    float2 w[2 * M + Q];
+    const auto load = [&](int i) {  // points i, i + 1 (i even where Q is)
+        if constexpr (Q % 2 == 0) {
+            const float4 q = *reinterpret_cast<const float4*>(win + i);
+            w[i] = make_float2(q.x, q.y);
+            w[i + 1] = make_float2(q.z, q.w);
+        } else {
+            if (i >= 0 && i < 2 * M + Q) w[i] = win[i];
+            if (i + 1 >= 0 && i + 1 < 2 * M + Q) w[i + 1] = win[i + 1];
+        }
+    };
+    const auto stage = [&](int s) {
+        if (s > NS) return;
+        load(M - E - 2 * s);
+        load(M + Q - 2 + E + 2 * s);
+    };
+#pragma unroll
+    for (int i = M - E; i < M + Q + E; i += 2) {
+        if (Q % 2 == 0 || i + 1 < M + Q) load(i);
+        else w[i] = win[i];
+    }
+#pragma unroll
+    for (int s = 1; s <= AHEAD; ++s) stage(s);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) o[q] = CONJ ? cmulf_conj(h[q][0], w[M + q]) : cmulf(h[q][0], w[M + q]);
+    float2 odd[Q] = {};
+    // (the outputs are pinned: left alone, the compiler sums one after the other and keeps
+    // the whole window in registers for it)
+    const auto tap = [&](int n) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const float2 s = cadd(w[M + q - n], w[M + q + n]);
+            float2& to = CONJ && n % 2 ? odd[q] : o[q];
+            to = CONJ ? cfmaf_conj(h[q][n], s, to) : cfmaf(h[q][n], s, to);
+            asm volatile("" : "+v"(to.x), "+v"(to.y));
+        }
+    };
+    if constexpr (E == 1) tap(1);
+    if (NS > 0) beside(0);
+#pragma unroll
+    for (int s = 1; s <= NS; ++s) {
+        __builtin_amdgcn_sched_barrier(0);
+        stage(s + AHEAD);
+        const int n = E + 2 * s - 1;
+        tap(n);
+        if (n + 1 <= M) tap(n + 1);
+        if (s < NS) beside(s);
+    }
+    if constexpr (CONJ)
+#pragma unroll
+        for (int q = 0; q < Q; ++q) o[q] = cadd(o[q], odd[q]);
+}
+
+// Stage after which taps 2 i and 2 i + 1 are loaded anew where one set is all there is:
+// the end of the group of stages that uses them last.
+template <int M, int Q>
+constexpr int refill_stage(int i)
+{
+    const int last = 2 * i + 1 <= kCentre<M, Q> ? 0 : (2 * i + 2 - kCentre<M, Q>) / 2;
+    const int g = last / kRefillStages * kRefillStages + kRefillStages - 1;
+    return g < kStages<M, Q> ? g : kStages<M, Q>;
+}
+
+// Taps 2 i and 2 i + 1 of a table row.
+template <int M>
+__device__ __forceinline__ void load_pair(float2 (&h)[M + 1], const float2* row, int i)
+{
+    const v4f v = tap_pair(row, 2 * i, 2 * i + 1 <= M);
+    h[2 * i] = make_float2(v.x, v.y);
+    if (2 * i + 1 <= M) h[2 * i + 1] = make_float2(v.z, v.w);
 }
 
 }  // namespace
