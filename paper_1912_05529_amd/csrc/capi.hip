@@ -500,10 +500,11 @@ int run_batch(const mig_section* secs, int nsec, const float2* tab, const mig_ta
         set_reducer_limits(a, tn);
         a.nsec = (int)g.secs.size();
         a.nitems = (int)g.items.size();
-        // Reducers only where the items leave them CUs, as for one section (run_extrap):
-        // beside more items than CUs there were 8 of them, which took longer over the
-        // rows than the rest of the launch (16 uneven sections of 256 to
-        // 2048 points: 18.7 -> 7.83 ms).
+        // Reducers where the caller asks for them, or the items leave them CUs, as for one
+        // section (run_extrap): beside more items than CUs there were 8 of them by
+        // default, which took longer over the rows than the rest of the launch (16 uneven
+        // sections of 256 to 2048 points: 18.7 -> 7.8 ms; 32 of them, an eighth of the
+        // CUs, come within a few percent of rows summed afterwards either way).
         const bool tuned = tn.nred > 0 || tn.stall_us > 0 || tn.flags != 0;
         const bool beside = tuned || (g.kind != 0 && device_cus() - a.nitems >= kReducerCus);
         a.ntasks = beside ? (int)g.tasks.size() : 0;

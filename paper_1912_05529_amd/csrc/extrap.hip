@@ -295,7 +295,7 @@ __device__ __forceinline__ void store_partial_q(float* pr, const float2 (&o)[Q],
 // SIMD with two waves sets the pace), while Q = 3 gives 6 to 8 waves and three
 // quarters of the work per wave.  Bound by the FP32 instruction rate and, where
 // waves refill, by the L1's data path.  1501 points, 300 depths, 101 frequencies:
-// layered 587 -> 541 us, a velocity that varies from point to point 782 -> 705 us.
+// layered 587 -> 499 us, a velocity that varies from point to point 782 -> 672 us.
 template <int M, int Q, bool ROWS>
 __global__ void __launch_bounds__(512) k_extrap_wide(BatchArgs a)
 {
@@ -355,6 +355,14 @@ __global__ void __launch_bounds__(512) k_extrap_wide(BatchArgs a)
         Refill<Q> next;
         next.look_up(a, ar, sn);
         slowness(k + 2, sn);
+        // Q = 3 stores a row at the start of the step after: which of its single-float
+        // stores are issued is not known to the compiler, so the next wait for a load is
+        // for them too (stored at the end of the step, 12 sections of 1100 to 1500 points
+        // took 10.2 ms instead of 9.5 ms)
+        if (ROWS && Q == 3 && k >= 1) {
+            store_partial_q<Q>(pr, o, ok);
+            pr += row;
+        }
         // after stage s: the pairs of taps that it and the stages before were the last to use
         constexpr int NS = kStages<M, Q>;
         const auto refill = [&](int s) {
@@ -375,13 +383,16 @@ __global__ void __launch_bounds__(512) k_extrap_wide(BatchArgs a)
         refill(NS);
         if (ROWS) {
             if (publishes_at(k)) wait_vmem_all();
-            store_partial_q<Q>(pr, o, ok);
-            pr += row;
+            if (Q != 3) {
+                store_partial_q<Q>(pr, o, ok);
+                pr += row;
+            }
         }
         __syncthreads();
         if (ROWS && publishes_at(k)) publish_block(a, S, k / kPublish - 1);
     }
     if (ROWS) {
+        if (Q == 3) store_partial_q<Q>(pr, o, ok);
         wait_vmem_all();
         __syncthreads();
         for (int b = published_in_loop(S.nsteps); b * kPublish < S.nsteps; ++b) publish_block(a, S, b);
