@@ -411,7 +411,7 @@ __device__ __forceinline__ void fold_step(const AdjArgs& a, float2* sm, float4* 
             const float2* row = a.tab + (size_t)j[q] * (M + 1);
 #pragma unroll
             for (int i = 0; 2 * i <= M; ++i)
-                if (refill_stage<M, 2>(i) == s) load_pair<M>(h[q], row, i);
+                if (refill_stage<M, 2, kRefillStages>(i) == s) load_pair<M>(h[q], row, i);
         }
     };
     const int LB = F.LB;

@@ -503,7 +503,7 @@ int run_batch(const mig_section* secs, int nsec, const float2* tab, const mig_ta
         // Reducers where the caller asks for them, or the items leave them CUs, as for one
         // section (run_extrap): beside more items than CUs there were 8 of them by
         // default, which took longer over the rows than the rest of the launch (16 uneven
-        // sections of 256 to 2048 points: 18.7 -> 7.8 ms; 32 of them, an eighth of the
+        // sections of 256 to 2048 points: 18.7 -> 7.4 ms; 32 of them, an eighth of the
         // CUs, come within a few percent of rows summed afterwards either way).
         const bool tuned = tn.nred > 0 || tn.stall_us > 0 || tn.flags != 0;
         const bool beside = tuned || (g.kind != 0 && device_cus() - a.nitems >= kReducerCus);

@@ -295,7 +295,7 @@ __device__ __forceinline__ void store_partial_q(float* pr, const float2 (&o)[Q],
 // SIMD with two waves sets the pace), while Q = 3 gives 6 to 8 waves and three
 // quarters of the work per wave.  Bound by the FP32 instruction rate and, where
 // waves refill, by the L1's data path.  1501 points, 300 depths, 101 frequencies:
-// layered 587 -> 499 us, a velocity that varies from point to point 782 -> 672 us.
+// layered 587 -> 493 us, a velocity that varies from point to point 782 -> 675 us.
 template <int M, int Q, bool ROWS>
 __global__ void __launch_bounds__(512) k_extrap_wide(BatchArgs a)
 {
@@ -366,13 +366,13 @@ __global__ void __launch_bounds__(512) k_extrap_wide(BatchArgs a)
         // after stage s: the pairs of taps that it and the stages before were the last to use
         constexpr int NS = kStages<M, Q>;
         const auto refill = [&](int s) {
-            if ((s % kRefillStages != kRefillStages - 1 && s != NS) || !next.any) return;
+            if ((s % kRefillStagesWide != kRefillStagesWide - 1 && s != NS) || !next.any) return;
 #pragma unroll
             for (int q = 0; q < Q; ++q) {
                 const float2* row = a.tab + (size_t)next.j[q] * (M + 1);
 #pragma unroll
                 for (int i = 0; 2 * i <= M; ++i)
-                    if (refill_stage<M, Q>(i) == s) load_pair<M>(h[q], row, i);
+                    if (refill_stage<M, Q, kRefillStagesWide>(i) == s) load_pair<M>(h[q], row, i);
             }
         };
         firq<M, Q>(sm + (k & 1) * LB + x0, h, o, refill);

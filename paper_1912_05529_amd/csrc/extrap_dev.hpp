@@ -264,6 +264,10 @@ __device__ __forceinline__ v4f tap_pair(const float2* row, int n, bool two)
 // costs waves that refill nothing 3 %; a FIR of its own for waves that refill makes the
 // compiler move whole tap sets where the two meet).
 constexpr int kRefillStages = 3;
+// The same in kernels of three and four outputs per thread, whose groups are larger (2000
+// points, 300 depths, 150 frequencies: layered 721 -> 695 us, 974 -> 934 us where the
+// velocity varies from point to point).
+constexpr int kRefillStagesWide = 2;
 
 // Q adjacent outputs x0..x0+Q-1 from the window w[i] = P[x0 - M + i], i = 0..2M+Q-1.
 // Even Q: x0 is even, so the window is read with 16-byte LDS loads; odd Q (x0 of either
@@ -343,11 +347,11 @@ __device__ __forceinline__ void firq(const float2* __restrict__ win, const float
 
 // Stage after which taps 2 i and 2 i + 1 are loaded anew where one set is all there is:
 // the end of the group of stages that uses them last.
-template <int M, int Q>
+template <int M, int Q, int GROUP>
 constexpr int refill_stage(int i)
 {
     const int last = 2 * i + 1 <= kCentre<M, Q> ? 0 : (2 * i + 2 - kCentre<M, Q>) / 2;
-    const int g = last / kRefillStages * kRefillStages + kRefillStages - 1;
+    const int g = last / GROUP * GROUP + GROUP - 1;
     return g < kStages<M, Q> ? g : kStages<M, Q>;
 }
 
