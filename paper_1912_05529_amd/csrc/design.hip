@@ -9,7 +9,7 @@
 // and a final scale that bounds |H| below one for every wavenumber (Bernstein's
 // inequality for trigonometric polynomials).  The formulas are in mig.h.
 //
-// Mapping (k_design, both dimensions): a workgroup designs EB = 1 or 2 entries.  What
+// Mapping (k_design, both dimensions): a team of 1 to 3 waves designs EB = 1 or 2 entries.  What
 // costs is the normal matrix: K (K+1) / 2 + 2 K sums over the design grid, 31 times per
 // entry.  Each sum runs over the grid in increasing order (another order moves the
 // fitted table by 1e-10: the fit's conditioning), so a sum is one thread's; a thread
@@ -17,8 +17,8 @@
 // point 4 basis values and a weight per entry from LDS for 10 operations per entry.
 // The basis streams through LDS in chunks of 64 grid points; the response |H| that
 // reweights a point is evaluated from the same chunk, just before the chunk is summed.
-// The system is solved by one wave (or half of one) per entry: a row per lane in
-// registers, one LDS exchange of the current column per elimination step, the
+// The system is solved by one wave (or half of one) per entry: the rest of a row per lane
+// in registers, one LDS exchange of the current column per elimination step, the
 // right-hand sides as two more rows.
 #include "common.hpp"
 
@@ -130,6 +130,14 @@ __host__ __device__ constexpr int design_points(int L, bool two_d) { return two_
 // two entries, 102 at 24, 168 at 32).
 __host__ __device__ constexpr int design_waves(int KT) { return KT <= 18 ? 1 : (KT <= 24 ? 2 : 3); }
 
+// Teams of that many waves in a workgroup, at most: each designs its own entries.  With
+// 256 registers two waves fit on a SIMD, and workgroups of one or two waves that share a
+// CU are put on the same SIMDs while the others idle (11 x 11 taps, 1024 entries: 8.75
+// ms); the four waves of one workgroup are spread over the four (6.15 ms: teams of two
+// waves then meet at the same barriers).  Where two teams of two waves per CU are all
+// there is, each wave asks for a SIMD of its own instead (5.79 ms; SOLO).
+__host__ __device__ constexpr int design_teams(int KT) { return 4 / design_waves(KT); }
+
 constexpr int kDesignChunk = 64;  // grid points per chunk of the basis
 
 // A grid point's row in LDS, in doubles: KT basis values (an even count), the targets
@@ -161,12 +169,12 @@ __host__ __device__ inline DesignLds design_lds(int L, int KT, int eb, bool two_
     o.d = at;
     at += two_d ? 2 * np * eb : 0;
     o.x = at;
-    at += eb * 4 * (KT + 2);
+    at += eb * 2 * (KT + 8);
     o.h = at;
     at += eb * 2 * KT;
     o.a = o.g = at;
     const int rows = kDesignChunk * design_stride(KT, eb) + 2, sys = eb * (KT + 2) * (KT | 1);
-    o.total = at + (rows > sys ? rows : sys);
+    o.total = (at + (rows > sys ? rows : sys) + 1) & ~1;
     return o;
 }
 
@@ -180,24 +188,27 @@ __device__ __forceinline__ void wave_lds_fence()
 
 // Cholesky of the lower triangle G (rows of stride KT | 1) with the right-hand sides
 // as rows KT and KT + 1, then the back substitution, by the lanes r = 0 .. KT+1 of one
-// wave or half of one: lane r keeps row r in registers (rows K .. KT-1 are the
-// identity's) and per column the lanes exchange their column values and diagonals
-// through x once.  Every element sees its subtractions in the order of a sequential
-// Cholesky and substitution.
+// wave or half of one: lane r keeps what is left of row r in registers, shifted by a
+// place per column (so that the columns are a loop: unrolled they took the kernel to 512
+// registers and spills), and per column the lanes exchange their column values and
+// diagonals through x once.  Every element sees its subtractions in the order of a
+// sequential Cholesky and substitution.
+constexpr int kSolveAhead = 8;  // products read at a time in the substitution
 template <int KT>
-__device__ __forceinline__ void design_solve(const double* G, v2f64* x, v2f64* h, int K, int r, int* fail)
+__host__ __device__ constexpr int design_exchange() { return KT + kSolveAhead; }  // pairs
+
+template <int KT>
+__device__ __forceinline__ void design_solve(double* G, v2f64* x, v2f64* h, int K, int r, int* fail)
 {
 #pragma clang fp contract(off)
     // a value the compiler cannot see through: what follows from it (a mask per column)
     // is formed here each time, not kept in registers over the passes
-    asm volatile("" : "+v"(r));
-    constexpr int LD = KT | 1;
+    asm volatile("" : "+v"(r), "+s"(K));
+    constexpr int LD = KT | 1, U = kSolveAhead;
     const bool rhs = r == KT || r == KT + 1, in = r < K;
-    const double* const row = G + (rhs || in ? r : 0) * LD;
-    // columns are exchanged as pairs; scheduling barriers keep the registers of the
-    // values in flight to a few pairs
+    double* const row = G + (rhs || in ? r : 0) * LD;
     double* const col = reinterpret_cast<double*>(x);
-    double* const dg = col + KT + 2 + (KT & 1);
+    double* const dg = col + KT + 2;
     double g[KT];
 #pragma unroll
     for (int q = 0; q < KT; ++q) {
@@ -206,64 +217,84 @@ __device__ __forceinline__ void design_solve(const double* G, v2f64* x, v2f64* h
         if (q % 8 == 7) __builtin_amdgcn_sched_barrier(0);
     }
     double diag = in ? row[in ? r : 0] : 1.0;
-    double pivot = G[0];
     bool bad = false;
-#pragma unroll
-    for (int m = 0; m < KT; ++m) {
-        if (!(pivot > 0.0)) {
-            bad = true;
-            pivot = 1.0;
-        }
-        const double d = sqrt(pivot);
-        const double l = r == m ? d : g[m] / d;
-        g[m] = l;
-        if (r < KT + 2) {
-            col[r] = l;
-            dg[r] = diag;
-        }
+    // A column's values v after division by the root of its pivot.  (The empty statement
+    // keeps the division out of a branch of its own.)
+    const auto divided = [&](int m, double v, double pivot) {
+        bad = bad || (m < K && !(pivot > 0.0));
+        const double d = sqrt(pivot > 0.0 ? pivot : 1.0);
+        v = v / d;
+        asm volatile("" : "+v"(v));
+        return r == m ? d : v;
+    };
+    double l = divided(0, g[0], G[0]);
+    // lanes without a row: places that no one reads
+    double* const my_col = col + (r < KT + 2 ? r : 2 * KT + 4);
+    double* const my_dg = r < KT + 2 ? dg + r : col + 2 * KT + 5;
+    for (int m = 0; m < K; ++m) {  // g[i]: column m + i
+        *my_col = l;
+        *my_dg = diag;
+        if (rhs || in) row[m] = l;  // (above the diagonal: values that no one reads)
         wave_lds_fence();
-        if (m + 1 < KT) {
-            const double n = col[m + 1 < KT ? m + 1 : m];
-            pivot = dg[m + 1 < KT ? m + 1 : m] - n * n;
-        }
+        const double n = col[m + 1], dn = dg[m + 1];
+        constexpr int NC = KT <= 24 ? KT : 16;
+        double c[NC];  // the other columns' values arrive beside the root
 #pragma unroll
-        for (int q = (m + 1) & ~1; q < KT; q += 2) {
-            const v2f64 c = x[q / 2];  // column values q, q + 1
-            if (q > m) g[q] -= l * c.x;
-            if (q + 1 < KT) g[q + 1 < KT ? q + 1 : q] -= l * c.y;
-            if (q % 8 == 6) __builtin_amdgcn_sched_barrier(0);
-        }
+        for (int i = 2; i < NC; ++i) c[i] = col[m + i];
+        __builtin_amdgcn_sched_barrier(0);
+        const double l_next = divided(m + 1, g[1 < KT ? 1 : 0] - l * n, dn - n * n);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 2; i < KT; ++i)  // past column K - 1: unused
+            g[i - 1] = g[i] - l * (i < NC ? c[i < NC ? i : 0] : col[m + i]);
         diag -= l * l;
+        l = l_next;
         wave_lds_fence();
     }
     if (bad && r == 0) *fail = 1;
-    // x: the transformed right-hand sides; then, per unknown m, the products of the
-    // lanes q > m that are subtracted from it
-    v2f64* const p = x + KT + 2;
-    if (rhs)
-#pragma unroll
-        for (int q = 0; q < KT; ++q) col[2 * q + r - KT] = g[q];
-    wave_lds_fence();
-    double xr = 0.0, xi = 0.0;
-#pragma unroll
-    for (int m = KT - 1; m >= 0; --m) {
-        if (r < KT) p[r] = v2f64{g[m] * xr, g[m] * xi};
+    // x: per unknown m, the products of the lanes q > m that are subtracted from it (zeros
+    // past the last); what the next unknown needs is read an unknown ahead
+    double xr = 0.0, xi = 0.0, lm = 0.0, d = G[(K - 1) * LD + K - 1];
+    v2f64 s = {G[KT * LD + K - 1], G[(KT + 1) * LD + K - 1]};
+    for (int m = K - 1; m >= 0; --m) {
+        if (r < KT + U) x[r] = v2f64{lm * xr, lm * xi};
         wave_lds_fence();
-        v2f64 s = x[m];
+        v2f64 v[U];
 #pragma unroll
-        for (int q = m + 1; q < KT; ++q) {
-            const v2f64 v = p[q];
-            s.x -= v.x;
-            s.y -= v.y;
-            if ((q - m) % 8 == 0) __builtin_amdgcn_sched_barrier(0);
+        for (int u = 0; u < U; ++u) v[u] = x[m + 1 + u];
+        const int mn = m > 0 ? m - 1 : 0;
+        const double d_next = G[mn * LD + mn];
+        const v2f64 s_next = {G[KT * LD + mn], G[(KT + 1) * LD + mn]};
+        const double row_next = row[mn];
+        for (int q = m + 1; q < K; q += U) {
+            v2f64 n[U];
+            const int next = q + U < K ? q + U : m + 1;
+#pragma unroll
+            for (int u = 0; u < U; ++u) n[u] = x[next + u];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                s -= v[u];
+                v[u] = n[u];
+            }
         }
-        if (r == m) {
-            xr = s.x / g[m];
-            xi = s.y / g[m];
-            h[m] = v2f64{xr, xi};
-        }
+        const double yr = s.x / d, yi = s.y / d;
+        xr = r == m ? yr : xr;
+        xi = r == m ? yi : xi;
+        d = d_next;
+        s = s_next;
+        lm = in && r > mn ? row_next : 0.0;
         wave_lds_fence();
     }
+    if (in) h[r] = v2f64{xr, xi};
+}
+
+// Barrier of a team: of the workgroup, or within the wave (teams of one wave each go
+// their own way: in step, with all of them at the sums at once, 1-D designs take 10 % more).
+template <int W>
+__device__ __forceinline__ void team_sync()
+{
+    if constexpr (W == 1) wave_lds_fence();
+    else __syncthreads();
 }
 
 // Phase shift over dz at kz^2 = q (in units of dx), or the decay past the cutoff.  A
@@ -296,31 +327,41 @@ __device__ __forceinline__ void design_fetch(v2f64 (&pre)[NV], v2f64 (&dpre)[NE]
 }
 
 // Bound by instruction issue (one wave per SIMD: about 6 cycles per FP64 operation).
-// 35 taps, 2048 entries: 16.0 -> 2.82 ms per table; 11 x 11 taps, 1024 entries: 28.5 ->
-// 5.7 ms (before: one workgroup per entry, a thread per sum reading the basis from L2,
-// the solves on one thread).  Of a pass of two 35-tap entries the sums take 147 k of
-// 214 k cycles, the responses 29 k, the solves 21 k, the chunks' copies 13 k.
+// 35 taps, 2048 entries: 16.0 -> 2.98 ms per table; 11 x 11 taps, 1024 entries: 28.4 ->
+// 5.79 ms; 63 taps, 2048 entries: 51.0 -> 9.1 ms (before: one workgroup per entry, a
+// thread per sum reading the basis from L2, the solves on one thread).  Of a pass of two
+// 35-tap entries the sums take 152 k of 232 k cycles, the solves 28 k, the responses
+// 25 k, the chunks' copies 13 k.
 //
-// No branch that part of a wave takes holds the sums (threads past the tiles repeat
-// the first one's), and the loops keep within 256 registers: with a mask around them
-// and registers moved to the accumulation file inside, idle lanes came out with other
-// lanes' addresses.
-template <int EB, int KT, bool TWO_D>
-__global__ void __launch_bounds__(64 * design_waves(KT))
+// Every instance keeps to 256 registers, without accumulation registers, spills or
+// scratch (tests/test_build_resources.py holds it to that): a build of this kernel that
+// moved values to the accumulation file inside a branch of part of a wave gave that
+// wave's idle lanes wrong addresses, and what the compiler does there was not found out.
+// What it takes: columns of the solve as a loop, one point's coefficients read some at a
+// time, sums pinned where they are formed.  With 390-512 registers instead, the solve's
+// columns unrolled, the listed tables took 2.83, 5.72 and 14.7 ms.  (Threads past the
+// tiles repeat the first one's sums: no branch of part of a wave holds them.)
+template <int EB, int KT, bool TWO_D, bool SOLO>
+__global__ void __launch_bounds__(64 * design_waves(KT) * (SOLO ? 1 : design_teams(KT)))
+    __attribute__((amdgpu_waves_per_eu(SOLO ? 1 : 2, SOLO ? 1 : 8)))
 k_design(DesignParams P, const double* __restrict__ A, const double* __restrict__ C, v2f64* D,
          mig_c128* tab64, mig_c64* tab32, double* maxgain, double* passerr, int* status)
 {
 #pragma clang fp contract(off)
-    extern __shared__ v2f64 dyn2[];
-    double* const dyn = reinterpret_cast<double*>(dyn2);
+    extern __shared__ v2f64 smem2[];
     constexpr int W = design_waves(KT), T = 64 * W, CH = kDesignChunk;
     constexpr int RS = design_stride(KT, EB), RP = RS / 2, LD = KT | 1;
     constexpr int DC = design_target_col(KT), WC = design_weight_col(KT, EB);
-    __shared__ double s_red[EB][W];
-    __shared__ int s_fail[EB];
-    const int K = P.K, L = P.L, t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    __shared__ double s_red_[design_teams(KT)][EB][W];
+    __shared__ int s_fail_[design_teams(KT)][EB];
+    const int teams = blockDim.x / T, team = __builtin_amdgcn_readfirstlane(threadIdx.x / T);
+    const int K = P.K, L = P.L, t = threadIdx.x - team * T, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    double (&s_red)[EB][W] = s_red_[team];
+    int (&s_fail)[EB] = s_fail_[team];
     const int LL = TWO_D ? L * L : L, np = design_points(L, TWO_D);
     const DesignLds o = design_lds(L, KT, EB, TWO_D);
+    v2f64* const dyn2 = smem2 + team * (o.total / 2);
+    double* const dyn = reinterpret_cast<double*>(dyn2);
     double* const w = dyn + o.w;
     double* const rows = dyn + o.a;
     const v2f64* const rows2 = dyn2 + o.a / 2;
@@ -349,20 +390,21 @@ k_design(DesignParams P, const double* __restrict__ A, const double* __restrict_
     // LDS places of the basis values this thread copies per chunk (values past the
     // chunk's rows go to the place after them)
     constexpr int NV = (CH * KT / 2 + T - 1) / T;
-    int to[NV][2];
+    unsigned to[NV];  // two places in 16 bits each
 #pragma unroll
-    for (int v = 0; v < NV; ++v)
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int at = 2 * (v * T + t) + u, row = at / K;
-            to[v][u] = row < CH ? row * RS + at - row * K : CH * RS;
-        }
+    for (int v = 0; v < NV; ++v) {
+        const auto place = [&](int at) -> unsigned {
+            const int row = at / K;
+            return row < CH ? row * RS + at - row * K : CH * RS;
+        };
+        to[v] = place(2 * (v * T + t)) | place(2 * (v * T + t) + 1) << 16;
+    }
 
-    for (int gi = blockIdx.x; gi * EB < P.nk; gi += gridDim.x) {
-        // the entries of this workgroup (past the table's end: the last one again)
-        const int j0 = gi * EB;
-        v2f64* const Dg = TWO_D ? dyn2 + o.d / 2 : D + (size_t)blockIdx.x * EB * L;
-        __syncthreads();
+    for (int gi = blockIdx.x * teams; gi * EB < P.nk; gi += gridDim.x * teams) {
+        // the entries of this team (past the table's end: the last one again)
+        const int j0 = (gi + team) * EB;
+        v2f64* const Dg = TWO_D ? dyn2 + o.d / 2 : D + (size_t)(blockIdx.x * teams + team) * EB * L;
+        team_sync<W>();
         for (int v = t; v < np * EB; v += T) {
             const int e = v / np, x = v - e * np;
             const int j = j0 + e < P.nk ? j0 + e : P.nk - 1;
@@ -387,7 +429,7 @@ k_design(DesignParams P, const double* __restrict__ A, const double* __restrict_
         }
         for (int v = t; v < EB * KT; v += T) hs[v] = v2f64{0.0, 0.0};  // coefficients past K
         if (t < EB) s_fail[t] = 0;
-        __syncthreads();
+        team_sync<W>();
 
         for (int it = 0; it <= P.nreweight; ++it) {
             double acc[EB][2][2];
@@ -405,17 +447,17 @@ k_design(DesignParams P, const double* __restrict__ A, const double* __restrict_
             design_fetch<NV, NE, T, TWO_D>(pre, dpre, A, Dg + e0 * LL, 0, LL, K, t, ip);
             for (int c0 = 0; c0 < LL; c0 += CH) {
                 const int n = LL - c0 < CH ? LL - c0 : CH;
-                __syncthreads();  // the previous chunk has been summed
+                team_sync<W>();  // the previous chunk has been summed
                 v2f64 dn[NE];
 #pragma unroll
                 for (int v = 0; v < NV; ++v) {
-                    rows[to[v][0]] = pre[v].x;
-                    rows[to[v][1]] = pre[v].y;
+                    rows[to[v] & 0xffffu] = pre[v].x;
+                    rows[to[v] >> 16] = pre[v].y;
                 }
 #pragma unroll
                 for (int e = 0; e < NE; ++e) dn[e] = dpre[e];
                 design_fetch<NV, NE, T, TWO_D>(pre, dpre, A, Dg + e0 * LL, c0 + CH < LL ? c0 + CH : 0, LL, K, t, ip);
-                __syncthreads();
+                team_sync<W>();
                 int x = c0 + ip < LL ? c0 + ip : LL - 1;
                 asm volatile("" : "+v"(x));
                 bool mirrored = false;
@@ -424,59 +466,69 @@ k_design(DesignParams P, const double* __restrict__ A, const double* __restrict_
                     mirrored = i > q;  // its mirror image came first and updates the weight
                     x = mirrored ? i * (i + 1) / 2 + q : q * (q + 1) / 2 + i;
                 }
-                double wv[NE];
-#pragma unroll
-                for (int e = 0; e < NE; ++e) wv[e] = w[(e0 + e) * np + x];
                 if (it > 0 && mine) {
                     // response of the last fit, and the weights where it exceeds one
                     const v2f64* const a2 = rows2 + ip * RP;
                     double Hr[NE] = {}, Hi[NE] = {};
+                    // some coefficients (those past K are zero) are read while those
+                    // before them are summed
+                    constexpr int B = NE == 2 ? 2 : 4;
+                    struct Coef {
+                        v2f64 a[B / 2], h[NE][B];
+                    };
+                    const auto get = [&](Coef& c, int q) {
 #pragma unroll
-                    for (int q = 0; q < KT; q += 2) {  // coefficients past K are zero
-                        const v2f64 a = a2[q / 2];
+                        for (int u = 0; u < B; ++u)
+                            if (q + u < KT) {
+                                if (u % 2 == 0) c.a[u / 2] = a2[(q + u) / 2];
 #pragma unroll
-                        for (int e = 0; e < NE; ++e) {
-                            const v2f64 h0 = hs[(e0 + e) * KT + q];
-                            Hr[e] += a.x * h0.x;
-                            Hi[e] += a.x * h0.y;
-                            if (q + 1 < KT) {
-                                const v2f64 h1 = hs[(e0 + e) * KT + (q + 1 < KT ? q + 1 : q)];
-                                Hr[e] += a.y * h1.x;
-                                Hi[e] += a.y * h1.y;
+                                for (int e = 0; e < NE; ++e) c.h[e][u] = hs[(e0 + e) * KT + q + u];
                             }
-                        }
-                        if (q % 6 == 4) __builtin_amdgcn_sched_barrier(0);
+                    };
+                    Coef now, next;
+                    get(now, 0);
+#pragma unroll
+                    for (int q = 0; q < KT; q += B) {
+                        get(next, q + B);
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int u = 0; u < B; ++u)
+                            if (q + u < KT)
+#pragma unroll
+                                for (int e = 0; e < NE; ++e) {
+                                    const double a = u % 2 == 0 ? now.a[u / 2].x : now.a[u / 2].y;
+                                    Hr[e] += a * now.h[e][u].x;
+                                    Hi[e] += a * now.h[e][u].y;
+                                }
+                        // (sunk into the branch below, the sums would leave every value
+                        // read above it in registers)
+#pragma unroll
+                        for (int e = 0; e < NE; ++e) asm volatile("" : "+v"(Hr[e]), "+v"(Hi[e]));
+                        __builtin_amdgcn_sched_barrier(0);
+                        now = next;
                     }
 #pragma unroll
                     for (int e = 0; e < NE; ++e)
                         // clearly below one: no excess (hypot errs by an ulp)
                         if (ip < n && !mirrored && !(Hr[e] * Hr[e] + Hi[e] * Hi[e] < 1.0 - 1e-12)) {
                             const double excess = hypot(Hr[e], Hi[e]) - 1.0;
-                            if (excess > 0.0) {
-                                wv[e] = wv[e] * (1.0 + P.beta * excess / P.tau);
-                                w[(e0 + e) * np + x] = wv[e];
-                            }
+                            double& we = w[(e0 + e) * np + x];
+                            if (excess > 0.0) we = we * (1.0 + P.beta * excess / P.tau);
                         }
                 }
-                if (TWO_D) {
-                    __syncthreads();  // both images of a point may lie in this chunk
-#pragma unroll
-                    for (int e = 0; e < NE; ++e) {
-                        wv[e] = w[(e0 + e) * np + x];
-                        dn[e] = Dg[(e0 + e) * np + x];
-                    }
-                }
+                if (TWO_D) team_sync<W>();  // both images of a point may lie in this chunk
                 if (mine)
 #pragma unroll
                     for (int e = 0; e < NE; ++e) {
-                        rows[ip * RS + WC + e0 + e] = wv[e];
-                        *reinterpret_cast<v2f64*>(rows + ip * RS + DC + 2 * (e0 + e)) = dn[e];
+                        rows[ip * RS + WC + e0 + e] = w[(e0 + e) * np + x];
+                        *reinterpret_cast<v2f64*>(rows + ip * RS + DC + 2 * (e0 + e)) =
+                            TWO_D ? Dg[(e0 + e) * np + x] : dn[e];
                     }
-                __syncthreads();
+                team_sync<W>();
                 // Few waves share a SIMD here, so the order is explicit: U grid points'
                 // operands are read while the U before them are summed, and each point's
                 // products stand apart from their sums.
-                constexpr int U = 4;
+                constexpr int U = EB == 2 && W == 1 ? 3 : 4;  // (registers)
                 struct Ops {
                     v2f64 p, q;
                     double w[EB];
@@ -540,7 +592,7 @@ k_design(DesignParams P, const double* __restrict__ A, const double* __restrict_
                 }
             }
             // the systems take the rows' place
-            __syncthreads();
+            team_sync<W>();
             if (tile)
 #pragma unroll
                 for (int e = 0; e < EB; ++e) {
@@ -559,7 +611,7 @@ k_design(DesignParams P, const double* __restrict__ A, const double* __restrict_
                             }
                         }
                 }
-            __syncthreads();
+            team_sync<W>();
             // a wave per entry, or half a wave (KT <= 18: 32 lanes hold the KT + 2 rows)
             {
                 constexpr bool half = NE > 1;
@@ -567,10 +619,11 @@ k_design(DesignParams P, const double* __restrict__ A, const double* __restrict_
                 const int sr = half ? t & 31 : t & 63;
                 asm volatile("" : "+v"(se));
                 if (half || wave < EB)
-                    design_solve<KT>(dyn + o.g + se * (KT + 2) * LD, dyn2 + o.x / 2 + se * 2 * (KT + 2),
-                                     hs + se * KT, K, sr, &s_fail[se]);
+                    design_solve<KT>(dyn + o.g + se * (KT + 2) * LD,
+                                     dyn2 + o.x / 2 + se * design_exchange<KT>(), hs + se * KT, K, sr,
+                                     &s_fail[se]);
             }
-            __syncthreads();
+            team_sync<W>();
         }
 
         // Stability scale: |H|max <= max_grid |H| / cos(M pi / (2 Lc)) (in two dimensions
@@ -617,10 +670,21 @@ k_design(DesignParams P, const double* __restrict__ A, const double* __restrict_
                 for (int e = 0; e < EB; ++e) raise(e, Hr[e], Hi[e]);
             }
         } else {
-            for (int c = t; c < P.Lc; c += T) {
-                double cc[KT];
+            // a point's basis values are asked for while the point before is evaluated
+            // (where registers allow)
+            constexpr bool ahead = KT <= 24;
+            double cc[KT];
+            const auto get = [&](double (&v)[KT], int c) {
+                int Kc = K;
+                asm volatile("" : "+s"(Kc));  // (hoisted, the rows' offsets would fill the scalar registers)
 #pragma unroll
-                for (int q = 1; q < KT; ++q) cc[q] = C[(size_t)(q < K ? q : 0) * P.Lc + c];
+                for (int q = 1; q < KT; ++q) v[q] = C[(size_t)(q < Kc ? q : 0) * P.Lc + c];
+            };
+            if (ahead) get(cc, t < P.Lc ? t : 0);
+            for (int c = t; c < P.Lc; c += T) {
+                double next[KT];
+                if (ahead) get(next, c + T < P.Lc ? c + T : c);
+                else get(cc, c);
 #pragma unroll
                 for (int e = 0; e < EB; ++e) {
                     double Hr = hs[e * KT].x, Hi = hs[e * KT].y;
@@ -629,9 +693,16 @@ k_design(DesignParams P, const double* __restrict__ A, const double* __restrict_
                         const v2f64 hv = hs[e * KT + q];
                         Hr += cc[q] * hv.x;
                         Hi += cc[q] * hv.y;
+                        if (q % 8 == 7) {
+                            asm volatile("" : "+v"(Hr), "+v"(Hi));
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
                     }
                     raise(e, Hr, Hi);
                 }
+#pragma unroll
+                for (int q = 1; q < KT; ++q)
+                    if (ahead) cc[q] = next[q];
             }
         }
         auto block_max = [&](double (&v)[EB]) {
@@ -641,12 +712,12 @@ k_design(DesignParams P, const double* __restrict__ A, const double* __restrict_
                 for (int off = 32; off >= 1; off >>= 1) v[e] = fmax(v[e], __shfl_xor(v[e], off, 64));
                 if ((t & 63) == 0) s_red[e][t >> 6] = v[e];
             }
-            __syncthreads();
+            team_sync<W>();
 #pragma unroll
             for (int e = 0; e < EB; ++e)
 #pragma unroll
                 for (int q = 0; q < W; ++q) v[e] = fmax(v[e], s_red[e][q]);
-            __syncthreads();
+            team_sync<W>();
         };
         block_max(g);
         const double cb = cos((double)P.M * kPi / (2.0 * (double)P.Lc));
@@ -705,29 +776,47 @@ k_design(DesignParams P, const double* __restrict__ A, const double* __restrict_
     }
 }
 
-template <int EB, int KT, bool TWO_D>
-int launch_design_as(const DesignParams& P, const double* A, const double* C, v2f64* D,
-                     mig_c128* tab64, mig_c64* tab32, double* maxgain, double* passerr, int* status,
-                     hipStream_t s)
+template <int EB, int KT, bool TWO_D, bool SOLO>
+int launch_design_teams(const DesignParams& P, const double* A, const double* C, v2f64* D,
+                        mig_c128* tab64, mig_c64* tab32, double* maxgain, double* passerr, int* status,
+                        int groups, int teams, size_t lds, hipStream_t s)
 {
-    const size_t lds = (size_t)design_lds(P.L, KT, EB, TWO_D).total * sizeof(double);
     if (lds > 64000 &&
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&k_design<EB, KT, TWO_D>),
+        hipFuncSetAttribute(reinterpret_cast<const void*>(&k_design<EB, KT, TWO_D, SOLO>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
         return MIG_E_DEVICE;
-    int blocks = P.nk / EB + (P.nk % EB != 0);
-    if (blocks > kDesignMaxSlots / EB) blocks = kDesignMaxSlots / EB;
-    hipLaunchKernelGGL((k_design<EB, KT, TWO_D>), dim3(blocks), dim3(64 * design_waves(KT)), lds, s,
-                       P, A, C, D, tab64, tab32, maxgain, passerr, status);
+    int blocks = groups / teams + (groups % teams != 0);
+    if (blocks > kDesignMaxSlots / (EB * teams)) blocks = kDesignMaxSlots / (EB * teams);
+    hipLaunchKernelGGL((k_design<EB, KT, TWO_D, SOLO>), dim3(blocks), dim3(64 * design_waves(KT) * teams),
+                       lds, s, P, A, C, D, tab64, tab32, maxgain, passerr, status);
     return hipGetLastError() == hipSuccess ? MIG_OK : MIG_E_DEVICE;
 }
 
-// Loops over coefficients are KT long (zeros past K).  Two entries per workgroup once
+template <int EB, int KT, bool TWO_D>
+int launch_design_as(const DesignParams& P, const double* A, const double* C, v2f64* D,
+                     mig_c128* tab64, mig_c64* tab32, double* maxgain, double* passerr, int* status,
+                     int cus, hipStream_t s)
+{
+    const size_t lds = (size_t)design_lds(P.L, KT, EB, TWO_D).total * sizeof(double);
+    const int groups = P.nk / EB + (P.nk % EB != 0);
+    // teams of two waves, two of them per CU
+    if constexpr (design_waves(KT) == 2)
+        if (groups > cus && groups <= 2 * cus)
+            return launch_design_teams<EB, KT, TWO_D, true>(P, A, C, D, tab64, tab32, maxgain, passerr,
+                                                            status, groups, 1, lds, s);
+    // as many teams as keep every CU busy, within its LDS
+    int teams = design_teams(KT);
+    while (teams > 1 && (teams * lds > 159 * 1024 || (long long)(teams - 1) * cus >= groups)) --teams;
+    return launch_design_teams<EB, KT, TWO_D, false>(P, A, C, D, tab64, tab32, maxgain, passerr, status,
+                                                     groups, teams, teams * lds, s);
+}
+
+// Loops over coefficients are KT long (zeros past K).  Two entries per team once
 // single ones would put more than one wave on a SIMD: a thread's sums of two entries
 // share their basis reads and fill one wave's issue slots better than two waves do
-// (35 taps, 2048 entries: 2.82 against 3.81 ms; 11 x 11 taps, 1024: 5.7 / 8.3 ms); below
-// that the second entry only lengthens the work of each wave (25 taps, 512 entries: 2.58
-// against 1.85 ms; 9 x 9 taps, 1024: 5.9 / 4.2 ms).
+// (with one wave per SIMD, 35 taps, 2048 entries: 2.82 against 3.81 ms; 11 x 11 taps,
+// 1024: 5.7 / 8.3 ms); below that the second entry only lengthens the work of each wave
+// (25 taps, 512 entries: 2.58 against 1.85 ms; 9 x 9 taps, 1024: 5.9 / 4.2 ms).
 template <int KT, bool TWO_D>
 int launch_design_kt(const DesignParams& P, const double* A, const double* C, v2f64* D,
                      mig_c128* tab64, mig_c64* tab32, double* maxgain, double* passerr, int* status,
@@ -738,8 +827,8 @@ int launch_design_kt(const DesignParams& P, const double* A, const double* C, v2
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         cus = 256;
     return (long long)P.nk * design_waves(KT) > 4LL * cus
-               ? launch_design_as<2, KT, TWO_D>(P, A, C, D, tab64, tab32, maxgain, passerr, status, s)
-               : launch_design_as<1, KT, TWO_D>(P, A, C, D, tab64, tab32, maxgain, passerr, status, s);
+               ? launch_design_as<2, KT, TWO_D>(P, A, C, D, tab64, tab32, maxgain, passerr, status, cus, s)
+               : launch_design_as<1, KT, TWO_D>(P, A, C, D, tab64, tab32, maxgain, passerr, status, cus, s);
 }
 
 }  // namespace
@@ -778,7 +867,7 @@ int launch_design_basis(const mig_table_desc* d, double* A, double* C, hipStream
 
 size_t design_target_bytes(const mig_table_desc* d)
 {
-    const size_t slots = ((size_t)d->nk + 3) / 4 * 4;
+    const size_t slots = (size_t)d->nk + 8;  // the last workgroup's teams may pass the end
     return (slots < (size_t)kDesignMaxSlots ? slots : (size_t)kDesignMaxSlots) * d->ngrid * sizeof(double2);
 }
 
