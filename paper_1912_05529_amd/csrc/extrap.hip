@@ -347,6 +347,14 @@ __global__ void __launch_bounds__(512) k_extrap_wide(BatchArgs a)
     };
     double sn[Q];
     slowness(1, sn);
+    // Waited for here: left in flight, the one wait at the start of a step, for the first as
+    // for the others, would be for everything in flight, the row of the step before included
+    // (constant velocity, 300 depths, 150 frequencies, reducers beside: 2000 points 579 ->
+    // 483 us, 1600 points 574 -> 480 us).  Q = 3, whose stores the compiler cannot count,
+    // keeps the wait for all (1300 points: 431 us, waited for here 511).
+    if constexpr (Q == 4)
+#pragma unroll
+        for (int q = 0; q < Q; ++q) asm volatile("" : "+v"(sn[q]));
     float* pr = live ? S.part + (size_t)r * S.ldp + x0 : a.trash + x0;
     const size_t row = live ? (size_t)S.nw * S.ldp : 0;
 
