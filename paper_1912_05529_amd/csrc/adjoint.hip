@@ -302,6 +302,41 @@ __device__ AdjChunk adj_lane_chunk(int lane, int M, int T)
     return c;
 }
 
+// Two outputs from the window w[i] = P[x0 - M + i], conjugated taps, the outermost taps
+// first: the small terms are added before the large ones, which halves the error of two
+// sums for even and odd taps (1024 points, 512 depths, 200 frequencies, against 64 bits:
+// 0.95e-6 -> 0.49e-6; centre first in one sum: 1.58e-6) and needs no second sum.  Points
+// that only the outer half of the taps uses are read first (constant velocity, all
+// points read at once 545 us, so 522 us).
+template <int M, int LO, int HI>
+__device__ __forceinline__ void fold_taps(const float2* __restrict__ win, const float2 (&h)[2][M + 1],
+                                          float2 (&o)[2])
+{
+    float2 w[2 * M + 2];
+#pragma unroll
+    for (int i = (M - HI) / 2; i <= (M + 1 + HI) / 2; ++i) {
+        if (LO > 0 && 2 * i > M - LO + 1 && 2 * i + 1 < M + LO) continue;  // no tap's here
+        const v4f q = *reinterpret_cast<const v4f*>(win + 2 * i);
+        w[2 * i] = make_float2(q.x, q.y);
+        w[2 * i + 1] = make_float2(q.z, q.w);
+    }
+#pragma unroll
+    for (int n = HI; n >= LO; --n)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const float2 u = n == 0 ? w[M + q] : cadd(w[M + q - n], w[M + q + n]);
+            o[q] = n == M ? cmulf_conj(h[q][n], u) : cfmaf_conj(h[q][n], u, o[q]);
+        }
+}
+
+template <int M>
+__device__ __forceinline__ void fold_fir(const float2* __restrict__ win, const float2 (&h)[2][M + 1],
+                                         float2 (&o)[2])
+{
+    fold_taps<M, M / 2 + 1, M>(win, h, o);
+    fold_taps<M, 0, M / 2>(win, h, o);
+}
+
 // LDS of the folded kernel: two planes, a row of corrections per wave (its
 // 128 outputs), then per parity the differences D_c[1..M] of each change
 // point followed by a zero.
@@ -370,10 +405,10 @@ struct FoldCarry {
     int nb;                   // change count of the row after (uniform)
     int jp;                   // (left | right << 16) entries of its change point i_ld
     double2 img;              // image row
-    double2 sn;               // slowness of the row after, flagged where it differs from this row
+    double2 sn;               // WIDE: slowness of the row after, flagged where it differs from this row
 };
 
-template <int M, int AHEAD>
+template <int M, bool WIDE>
 __device__ __forceinline__ void fold_step(const AdjArgs& a, float2* sm, float4* cw, float2* dh,
                                           const FoldState& F, const FoldLane<adj_chunk_len(M)>& CL,
                                           int k_in, float2 (&h)[2][M + 1], FoldCarry& C)
@@ -392,13 +427,10 @@ __device__ __forceinline__ void fold_step(const AdjArgs& a, float2* sm, float4* 
     const int n_build = C.nb;
     const int i_ld = F.i_ld, m_ld = F.m_ld;
     const bool build = k >= 1 && F.on && i_ld < n_build;
-    // taps of step k-1, where row k-1 differs from row k under some output of the wave:
-    // loaded for all its outputs as the FIR has used them for the last time (before: one
-    // masked block behind the FIR.  1501 points, 300 depths, 101 frequencies, layered:
-    // 752 -> 655 us; 1024 points, 512 depths, 200 frequencies: 791 us either way, there
-    // the waves with corrections set the pace)
-    const bool refills = k >= 1 && __builtin_amdgcn_ballot_w64(slowness_changed(C.sn.x) ||
-                                                               slowness_changed(C.sn.y)) != 0;
+    // WIDE: taps of step k-1, where row k-1 differs from row k under some output of the
+    // wave: loaded for all its outputs as the FIR has used them for the last time
+    const bool refills = WIDE && k >= 1 && __builtin_amdgcn_ballot_w64(slowness_changed(C.sn.x) ||
+                                                                       slowness_changed(C.sn.y)) != 0;
     int j[2] = {0, 0};
     if (refills) {
         j[0] = index_of_slowness(F.ar, a.b, a.nk, slowness_value(C.sn.x));
@@ -477,14 +509,15 @@ __device__ __forceinline__ void fold_step(const AdjArgs& a, float2* sm, float4* 
         hl = load_global(a.tab + (size_t)((unsigned)C.jp & 0xffffu) * (M + 1) + m_ld);
     }
     // loads for this step's end and the next step, branch-free (rows clamped;
-    // values past the top are unused): image row k-1 and its change points,
-    // the change count and entries of row k-2 and its slowness (flagged where
-    // it differs from row k-1) for the refills of the next step
+    // values past the top are unused): slowness row k-1 (flagged where it
+    // differs from row k) for the refill at the end of this step, or (WIDE) row
+    // k-2 for the refills of the next, image row k-1 and its change points, the
+    // change count and entries of row k-2
     double2 sn, img_n;
     int cnt_n, mp_n, jp_n;
     {
         const int ks = k >= 1 ? k - 1 : 0, kn = k >= 2 ? k - 2 : 0;
-        sn = load_global(reinterpret_cast<const double2*>(a.slow + (size_t)kn * a.ldp + F.x0));
+        sn = load_global(reinterpret_cast<const double2*>(a.slow + (size_t)(WIDE ? kn : ks) * a.ldp + F.x0));
         img_n = make_double2(a.image[(size_t)ks * nx + F.c0], a.image[(size_t)ks * nx + F.c1]);
         // vector loads: as scalar loads their completion would be tracked by
         // the counter the FIR's LDS waits use, and they would wait for them
@@ -499,7 +532,8 @@ __device__ __forceinline__ void fold_step(const AdjArgs& a, float2* sm, float4* 
     // corrections (read back and cleared: LDS keeps one wave's accesses in
     // order, the fence keeps the compiler from moving the read up)
     float2 o[2];
-    firq<M, 2, true, AHEAD>(Pin + F.x0, h, o, refill);
+    if constexpr (WIDE) firq<M, 2, true, 1>(Pin + F.x0, h, o, refill);
+    else fold_fir<M>(Pin + F.x0, h, o);
     float2 o0 = o[0], o1 = o[1];
     o0.x += (float)cimg.x;
     o1.x += (float)cimg.y;
@@ -522,11 +556,14 @@ __device__ __forceinline__ void fold_step(const AdjArgs& a, float2* sm, float4* 
         C.mask = __ballot(rel);
         const int c = __builtin_amdgcn_readfirstlane(cnt_n);
         C.nb = c < a.kmax ? c : a.kmax;
-        asm volatile("" : "+v"(mp_n), "+v"(jp_n), "+v"(img_n.x), "+v"(img_n.y), "+v"(sn.x), "+v"(sn.y));
+        asm volatile("" : "+v"(mp_n), "+v"(jp_n), "+v"(img_n.x), "+v"(img_n.y));
         C.mp = mp_n;
         C.jp = jp_n;
         C.img = img_n;
-        C.sn = sn;
+        if constexpr (WIDE) {
+            asm volatile("" : "+v"(sn.x), "+v"(sn.y));
+            C.sn = sn;
+        }
     }
     if (k >= 1) {
         // differences of row k-1 into the other cache (read from step k-1 on)
@@ -535,14 +572,26 @@ __device__ __forceinline__ void fold_step(const AdjArgs& a, float2* sm, float4* 
             dh[(kp * kAdjKmax + i_ld) * (M + 1) + m_ld - 1] = make_float2(hr.x - hl.x, hr.y - hl.y);
         }
     }
-    refill(kStages<M, 2>);
+    if constexpr (WIDE) {
+        refill(kStages<M, 2>);
+    } else if (k >= 1) {
+        // taps of step k-1 where row k-1 differs from row k; the FIR of the
+        // next step waits for them (mostly L1 hits: the rows of one frequency)
+        if (slowness_changed(sn.x))
+            load_taps_adj<M>(h[0], a.tab + (size_t)index_of_slowness(F.ar, a.b, a.nk, slowness_value(sn.x)) * (M + 1));
+        if (slowness_changed(sn.y))
+            load_taps_adj<M>(h[1], a.tab + (size_t)index_of_slowness(F.ar, a.b, a.nk, slowness_value(sn.y)) * (M + 1));
+    }
     __syncthreads();
 }
 
-// Up to 512 threads (1024 points), or 768: three waves per SIMD within 168 registers (up
-// to 1536 points; a fourth would spill; windows are read one stage ahead there, for
-// registers).  1501 points, 101 frequencies, 300 depths, 35 taps, layered: 3610 -> 655 us
-// (before: the general kernel, now 982 there).
+// Up to 512 threads (1024 points) with 256 registers, the taps that change loaded in one
+// masked block at a step's end; or 768 (1536 points, WIDE): three
+// waves per SIMD within 168 registers (4 of the 35-tap instance are spilled), the window
+// read one stage ahead and the taps loaded between the stages of the FIR.  1501 points, 101 frequencies, 300
+// depths, 35 taps, layered: 3610 -> 670 us (before: the general kernel, now 982 there; in
+// the first form 746).  1024 points, 200 frequencies, 512 depths: layered 782, constant
+// velocity 520 us (in the second form 806 and 558).
 constexpr int kFoldMaxThreads = 768;
 
 template <int M, int THREADS>
@@ -612,7 +661,7 @@ __global__ void __launch_bounds__(THREADS) k_demigrate_fold(AdjArgs a)
     C.sn = *reinterpret_cast<const double2*>(a.slow + (size_t)(k >= 1 ? k - 1 : 0) * a.ldp + F.x0);
     __syncthreads();
 
-    for (; k >= 0; --k) fold_step<M, THREADS <= 512 ? kStagesAhead : 1>(a, sm, cw, dh, F, CL, k, h, C);
+    for (; k >= 0; --k) fold_step<M, (THREADS > 512)>(a, sm, cw, dh, F, CL, k, h, C);
     const float2* P0 = sm + M;  // Q_0 is in plane 0
     if (F.ok0) a.out[(size_t)F.x0 * a.nw + r] = P0[F.x0];
     if (F.ok1) a.out[(size_t)(F.x0 + 1) * a.nw + r] = P0[F.x0 + 1];

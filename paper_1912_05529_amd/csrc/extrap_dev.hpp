@@ -283,8 +283,8 @@ constexpr int kCentre = Q % 2 == 0 && M % 2 ? 1 : 0;  // last tap of stage 0
 template <int M, int Q>
 constexpr int kStages = (M - kCentre<M, Q> + 1) / 2;  // stages after stage 0
 
-// CONJ: conjugated taps, and a sum each for even and odd taps (the adjoint; the forward
-// planes keep one sum in increasing order of taps).
+// CONJ: conjugated taps, and a sum each for even and odd taps (the adjoint of wide sections;
+// the forward planes keep one sum in increasing order of taps).
 template <int M, int Q, bool CONJ = false, int AHEAD = kStagesAhead, class F>
 __device__ __forceinline__ void firq(const float2* __restrict__ win, const float2 (&h)[Q][M + 1],
                                      float2 (&o)[Q], const F& beside)
