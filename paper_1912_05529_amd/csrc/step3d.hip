@@ -44,6 +44,7 @@ constexpr int kRows3 = 8;                    // x rows walked by each wave
 constexpr int kTileX3 = kWaves3 * kRows3;    // x rows per tile
 constexpr int kThreads3 = kWaves3 * 64;
 constexpr int kSlots3 = 4;                   // LDS tap slots per wave (see k_step3d)
+constexpr int kNearly3 = 24;                 // groups from which 32 partials are summed at a time
 constexpr int kSlotF2 = 32;                  // complex values per slot (>= unique taps)
 constexpr int kNoSlot = 7;                   // 3-bit slot code of a point without a slot
 
@@ -412,7 +413,7 @@ __device__ __forceinline__ void stage_rows(float2* Tb, __amdgpu_buffer_rsrc_t rp
     }
 }
 
-template <int M>
+template <int M, bool MANY>
 __global__ void __launch_bounds__(kThreads3) __attribute__((amdgpu_waves_per_eu(2)))
 k_step3d(Step3dArgs A)
 {
@@ -480,39 +481,47 @@ k_step3d(Step3dArgs A)
     // Image row of the previous depth step: this workgroup's share of the
     // tile, groups added in group order (the partials of the previous launch
     // are complete when this one starts).
-    // All partials of a point are asked for before the first is added (with 8 at a time
-    // the groups' round trips added up: 49 x 75 points, 41 depths, 25 frequencies 511 ->
-    // 497 us, 96 x 88, 60 depths, 82 frequencies 1210 -> 1109 us); no more places than
-    // there are groups, as nearly as three forms allow (32 for all: 256 x 256 points, 16
-    // groups, 12.83 -> 12.95 ms).
+    // MANY (kNearly groups and more): 32 partials of a point are asked for before the first
+    // is added while there are that many, or nearly (8 at a time, the groups' round trips
+    // add up: 49 x 75 points, 41 depths, 25 groups 502 -> 475 us, 96 x 88, 60 depths, 82
+    // groups 1202 -> 1108 us); the rest 8 at a time and no more than there are (places
+    // beyond the last group cost more than a second round trip: 24 x 24 points, 100 depths,
+    // 9 groups in 16 places 1112 us, so 1089 us; 33 groups in 64 places 1241 us, so 1155
+    // us).  A kernel of its own: the loop over 32 beside that over 8 costs volumes of few
+    // groups 1 % (9 groups: 1105 us).
     if (A.prev) {
         constexpr int pts = kTileX3 * kLanes3;
+        constexpr int kMany = 32, kFew = 8;  // partial loads in flight per thread
         const int share = (pts + A.ngroups - 1) / A.ngroups;
         const int e1 = (g + 1) * share < pts ? (g + 1) * share : pts;
-        auto sum = [&](auto BATCH) {
-            constexpr int kBatch = decltype(BATCH)::value;  // partial loads in flight per thread
-            for (int e = g * share + threadIdx.x; e < e1; e += kThreads3) {
-                const int x = x0 + e / kLanes3, yy = y0 + e % kLanes3;
-                if (x < A.nx && yy < A.ny) {
-                    const size_t p = (size_t)x * A.ny + yy;
-                    double s = 0.0;
-                    for (int q0 = 0; q0 < A.ngroups; q0 += kBatch) {
-                        double pv[kBatch];
+        for (int e = g * share + threadIdx.x; e < e1; e += kThreads3) {
+            const int x = x0 + e / kLanes3, yy = y0 + e % kLanes3;
+            if (x < A.nx && yy < A.ny) {
+                const size_t p = (size_t)x * A.ny + yy;
+                double s = 0.0;
+                int q0 = 0;
+                for (; MANY && A.ngroups - q0 >= kNearly3; q0 += kMany) {
+                    double pv[kMany];
 #pragma unroll
-                        for (int i = 0; i < kBatch; ++i)
-                            pv[i] = A.prev[(size_t)(q0 + i < A.ngroups ? q0 + i : A.ngroups - 1) * plane + p];
-                        __builtin_amdgcn_sched_barrier(0);  // every load issued before the first add
+                    for (int i = 0; i < kMany; ++i)
+                        pv[i] = A.prev[(size_t)(q0 + i < A.ngroups ? q0 + i : A.ngroups - 1) * plane + p];
+                    __builtin_amdgcn_sched_barrier(0);  // every load issued before the first add
 #pragma unroll
-                        for (int i = 0; i < kBatch; ++i)
-                            if (q0 + i < A.ngroups) s += pv[i];
-                    }
-                    A.prev_row[p] = s;
+                    for (int i = 0; i < kMany; ++i)
+                        if (q0 + i < A.ngroups) s += pv[i];
                 }
+                for (; q0 < A.ngroups; q0 += kFew) {
+                    double pv[kFew];
+#pragma unroll
+                    for (int i = 0; i < kFew; ++i)
+                        pv[i] = q0 + i < A.ngroups ? A.prev[(size_t)(q0 + i) * plane + p] : 0.0;
+#pragma unroll
+                    for (int i = 0; i < kFew; ++i)
+                        if (q0 + i < A.ngroups) s += pv[i];
+                }
+                A.prev_row[p] = s;
             }
-        };
-        if (A.ngroups <= 8) sum(std::integral_constant<int, 8>{});
-        else if (A.ngroups <= 16) sum(std::integral_constant<int, 16>{});
-        else sum(std::integral_constant<int, 32>{});
+        }
     }
 
 #pragma unroll
@@ -777,16 +786,23 @@ unsigned grid_for(size_t n)
 int step3d_tiles_x(int nx) { return (nx + kTileX3 - 1) / kTileX3; }
 int step3d_tiles_y(int ny) { return (ny + kLanes3 - 1) / kLanes3; }
 
+template <int M>
+static void launch_step3d_as(const Step3dArgs& a, hipStream_t s)
+{
+    const dim3 grid((unsigned)(a.tiles_x * a.tiles_y * a.ngroups));
+    if (a.ngroups >= kNearly3) hipLaunchKernelGGL((k_step3d<M, true>), grid, dim3(kThreads3), 0, s, a);
+    else hipLaunchKernelGGL((k_step3d<M, false>), grid, dim3(kThreads3), 0, s, a);
+}
+
 int launch_step3d(const Step3dArgs& a, int M, hipStream_t s)
 {
-    const unsigned nb = (unsigned)(a.tiles_x * a.tiles_y * a.ngroups);
     switch (M) {
-    case 0: hipLaunchKernelGGL(k_step3d<0>, dim3(nb), dim3(kThreads3), 0, s, a); break;
-    case 1: hipLaunchKernelGGL(k_step3d<1>, dim3(nb), dim3(kThreads3), 0, s, a); break;
-    case 2: hipLaunchKernelGGL(k_step3d<2>, dim3(nb), dim3(kThreads3), 0, s, a); break;
-    case 3: hipLaunchKernelGGL(k_step3d<3>, dim3(nb), dim3(kThreads3), 0, s, a); break;
-    case 4: hipLaunchKernelGGL(k_step3d<4>, dim3(nb), dim3(kThreads3), 0, s, a); break;
-    case 5: hipLaunchKernelGGL(k_step3d<5>, dim3(nb), dim3(kThreads3), 0, s, a); break;
+    case 0: launch_step3d_as<0>(a, s); break;
+    case 1: launch_step3d_as<1>(a, s); break;
+    case 2: launch_step3d_as<2>(a, s); break;
+    case 3: launch_step3d_as<3>(a, s); break;
+    case 4: launch_step3d_as<4>(a, s); break;
+    case 5: launch_step3d_as<5>(a, s); break;
     default: return MIG_E_ARG;
     }
     return hipGetLastError() == hipSuccess ? MIG_OK : MIG_E_DEVICE;
