@@ -330,8 +330,9 @@ typedef struct {
                                  (0 = the CUs the frequency workgroups leave
                                  idle, at least 8 and at most 32); never more
                                  than a quarter of the device's CUs.  With 0,
-                                 launches that leave fewer than 32 CUs idle
-                                 sum their rows afterwards instead           */
+                                 launches that leave fewer than 32 CUs idle,
+                                 and those of the general kernel, sum their
+                                 rows afterwards instead                     */
     int32_t stall_limit_us;   /* reducer stall limit in microseconds
                                  (0 = 20 s); see mig_workspace_status        */
     int32_t flags;            /* 0, or MIG_TUNE_FORCE_STALL                 */

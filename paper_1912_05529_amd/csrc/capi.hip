@@ -505,8 +505,8 @@ int run_batch(const mig_section* secs, int nsec, const float2* tab, const mig_ta
         // default, which took longer over the rows than the rest of the launch (16 uneven
         // sections of 256 to 2048 points: 18.7 -> 7.4 ms; 32 of them, an eighth of the
         // CUs, come within a few percent of rows summed afterwards either way).
-        const bool tuned = tn.nred > 0 || tn.stall_us > 0 || tn.flags != 0;
-        const bool beside = tuned || (g.kind != 0 && device_cus() - a.nitems >= kReducerCus);
+        const bool asked = tn.nred > 0 || tn.flags != 0;
+        const bool beside = asked || (g.kind != 0 && device_cus() - a.nitems >= kReducerCus);
         a.ntasks = beside ? (int)g.tasks.size() : 0;
         a.nred = g.nred < a.ntasks ? g.nred : a.ntasks;
         a.rows = 1;

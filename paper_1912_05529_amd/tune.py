@@ -6,7 +6,9 @@ frequency columns share a workgroup when nx is small), outputs per thread
 for sections of 1025..1536 points (three: 6-8 waves per frequency, or four:
 5-6 waves with more work each; the x-tile of a workgroup is always the whole
 section width, so this is the tile knob), and the number of reducer
-workgroups that form image rows beside the frequency workgroups.  Depth
+workgroups that form image rows beside the frequency workgroups (0: the
+library's choice, which is none of them for launches that fill the GPU,
+whose rows are summed afterwards).  Depth
 fusion is not a knob: all depth steps of a section always run in one launch
 (the plane never leaves LDS), which is the most fusion there is.  Each
 candidate is timed with HIP events on the current stream; the result is
@@ -23,7 +25,7 @@ from . import mig
 _cache: dict = {}
 
 OMEGAS_PER_GROUP = (1, 2, 4, 8)
-REDUCERS = (16, 32, 48)
+REDUCERS = (0, 16, 32, 48)
 OUTPUTS_MID = (3, 4)
 
 
