@@ -349,9 +349,9 @@ __global__ void __launch_bounds__(512) k_extrap_wide(BatchArgs a)
     slowness(1, sn);
     // Waited for here: left in flight, the one wait at the start of a step, for the first as
     // for the others, would be for everything in flight, the row of the step before included
-    // (constant velocity, 300 depths, 150 frequencies, reducers beside: 2000 points 579 ->
-    // 483 us, 1600 points 574 -> 480 us).  Q = 3, whose stores the compiler cannot count,
-    // keeps the wait for all (1300 points: 431 us, waited for here 511).
+    // (2000 points, 300 depths, 150 frequencies, constant velocity, rows stored at the end
+    // of a step: 579 -> 483 us).  Q = 3, whose stores the compiler cannot count, keeps the
+    // wait for all (1300 points: 431 us, waited for here 511).
     if constexpr (Q == 4)
 #pragma unroll
         for (int q = 0; q < Q; ++q) asm volatile("" : "+v"(sn[q]));
@@ -363,11 +363,13 @@ __global__ void __launch_bounds__(512) k_extrap_wide(BatchArgs a)
         Refill<Q> next;
         next.look_up(a, ar, sn);
         slowness(k + 2, sn);
-        // Q = 3 stores a row at the start of the step after: which of its single-float
-        // stores are issued is not known to the compiler, so the next wait for a load is
-        // for them too (stored at the end of the step, 12 sections of 1100 to 1500 points
-        // took 10.2 ms instead of 9.5 ms)
-        if (ROWS && Q == 3 && k >= 1) {
+        // A row is stored at the start of the step after, whose FIR it then runs beside:
+        // at the end of its step every wave stores just before the barrier that all wait
+        // at, behind the taps loaded last (2000 points, 300 depths, 150 frequencies,
+        // layered 672 -> 654 us, 1907 points, 200 depths, 100 frequencies, 19 taps 305 ->
+        // 286 us, batches of 1537 to 2048 points 6.44 -> 6.03 ms; three outputs, 1100 to
+        // 1500 points, 10.2 -> 9.5 ms)
+        if (ROWS && k >= 1) {
             store_partial_q<Q>(pr, o, ok);
             pr += row;
         }
@@ -391,16 +393,12 @@ __global__ void __launch_bounds__(512) k_extrap_wide(BatchArgs a)
         refill(NS);
         if (ROWS) {
             if (publishes_at(k)) wait_vmem_all();
-            if (Q != 3) {
-                store_partial_q<Q>(pr, o, ok);
-                pr += row;
-            }
         }
         __syncthreads();
         if (ROWS && publishes_at(k)) publish_block(a, S, k / kPublish - 1);
     }
     if (ROWS) {
-        if (Q == 3) store_partial_q<Q>(pr, o, ok);
+        store_partial_q<Q>(pr, o, ok);
         wait_vmem_all();
         __syncthreads();
         for (int b = published_in_loop(S.nsteps); b * kPublish < S.nsteps; ++b) publish_block(a, S, b);
