@@ -181,7 +181,7 @@ size_t extrap_head_bytes(int nx, int nw)
 // [slowness chunk x ldp doubles][partials chunk x nw x ldp floats].
 int run_extrap(const float2* src, float2* dst, const float* vel, const double* omega,
                const float2* tab, const mig_table_desc* d, int nx, int nw, int nsteps,
-               double* rows, void* ws, size_t ws_bytes, hipStream_t s, const Tuning& tn)
+               double* rows, void* ws, size_t ws_bytes, hipStream_t s)
 {
     const int ldp = row_stride(nx);
     const size_t head = extrap_head_bytes(nx, nw);
@@ -203,8 +203,7 @@ int run_extrap(const float2* src, float2* dst, const float* vel, const double* o
 
     const int M = (d->ntaps - 1) / 2;
     const int kind = extrap_kernel_kind(nx, M);
-    const int G = omegas_per_group(kind, nx, tn.G);
-    const int nitems = (nw + G - 1) / G;
+    const int nitems = nw;  // one frequency per workgroup
 
     BatchArgs a = {};
     a.one.omega = omega;
@@ -215,12 +214,12 @@ int run_extrap(const float2* src, float2* dst, const float* vel, const double* o
     a.one.nw = nw;
     a.one.ldp = ldp;
     a.one.nprod = nitems;
-    a.one.G = G;
+    a.one.G = 1;
     a.tab = tab;
     a.trash = trash;
     a.progress = cnt + kMaxBlocks;
     a.status = status;
-    set_reducer_limits(a, tn);
+    set_reducer_limits(a, Tuning{});
     a.nsec = 1;
     a.nitems = nitems;
     a.nk = d->nk;
@@ -255,12 +254,10 @@ int run_extrap(const float2* src, float2* dst, const float* vel, const double* o
         // frequencies 210 -> 192 us; but 601 points, 301 depths, 97 frequencies (70 MB)
         // 344 -> 353 us, 700 points, 512 depths, 200 frequencies 468 -> 495 us, and in
         // kind 2 2000 points, 60 depths, 100 frequencies (48 MB) 130 -> 133 us.
-        const bool tuned = tn.nred > 0 || tn.stall_us > 0 || tn.flags != 0;
         const bool few = kind != 2 && (size_t)cs * nw * nx * sizeof(float) <= kRowsAfter;
-        const bool beside = rows && nb > 1 && kind != 0 &&
-                            (tuned || (device_cus() - nitems >= kReducerCus && !few));
+        const bool beside = rows && nb > 1 && kind != 0 && device_cus() - nitems >= kReducerCus && !few;
         if (beside) {
-            const int nred = reducer_count(nitems, tn.nred);
+            const int nred = reducer_count(nitems, 0);
             a.parts = parts_of(nx);
             a.ntasks = (nb - 1) * a.parts;
             a.nred = nred < a.ntasks ? nred : a.ntasks;
@@ -275,9 +272,9 @@ int run_extrap(const float2* src, float2* dst, const float* vel, const double* o
         int rc = launch_slowness(a, cs, ldp, flag_distance(kind), s);
         if (rc == MIG_OK) {
             if (kind == 0) rc = launch_general(a, nx, s);
-            else if (extrap_narrow(kind, nx, G, nitems, device_cus()))
-                rc = launch_extrap(a, kind, G * threads_narrow(nx), true, s);
-            else rc = launch_extrap(a, kind, G * threads_per_omega(kind, nx), false, s);
+            else if (extrap_narrow(kind, nx, nitems, device_cus()))
+                rc = launch_extrap(a, kind, threads_narrow(nx), true, s);
+            else rc = launch_extrap(a, kind, threads_per_omega(kind, nx), false, s);
         }
         if (rc == MIG_OK && rows)
             rc = launch_rows(part, a.one.rows, beside ? (nb - 1) * kPublish : 0, cs, nx, nw, ldp, s);
@@ -298,6 +295,7 @@ struct BatchPlan {
     size_t bytes = 0;
     struct Group {
         int kind = 0, threads = 0, max_nx = 0, max_rows = 0, max_ldp = 0, nred = 0, parts = 1;
+        bool beside = false;  // reducers run beside the depth stepping
         std::vector<SecDev> secs;
         std::vector<ItemDev> items;
         std::vector<TaskDev> tasks;
@@ -329,11 +327,15 @@ bool sections_ok(const mig_section* secs, int nsec)
 
 // Relative time of one depth step of a workgroup item in kernel `kind`: the
 // busiest SIMD runs ceil(waves / 4) waves, each with q outputs per thread
-// (the general kernel: 4 waves, ceil(nx / 256) outputs per thread).  Only
+// (the general kernel: runs of 2 or 4 outputs in up to 12 waves).  Only
 // used to order reducer tasks.
 double step_cost(int kind, const SecDev& S)
 {
-    if (kind == 0) return (double)((S.nx + 255) / 256);
+    if (kind == 0) {
+        const int q = S.nx <= 2 * 768 ? 2 : 4;
+        const int waves = std::min(12, (S.nx + 64 * q - 1) / (64 * q));
+        return (double)((waves + 3) / 4 * q * ((S.nx + waves * 64 * q - 1) / (waves * 64 * q)));
+    }
     const int q = kind == 1 ? 2 : (kind == 2 ? 4 : 3);
     const int waves = S.G * threads_per_omega(kind, S.nx) / 64;
     return (double)((waves + 3) / 4 * q);
@@ -371,9 +373,8 @@ void plan_batch(const mig_section* secs, int nsec, const mig_table_desc* d, cons
         S.part = reinterpret_cast<float*>(base ? base + po : nullptr);
         S.cnt = reinterpret_cast<int*>((size_t)g.ncnt);  // offset, fixed up below
         g.ncnt += (S.nsteps + kPublish - 1) / kPublish;
-        const int tpo = threads_per_omega(kind, q.nx);
-        const int th = kind == 0 ? 256 : S.G * tpo;
-        g.threads = th > g.threads ? th : g.threads;
+        const int th = kind == 0 ? 0 : S.G * threads_per_omega(kind, q.nx);
+        g.threads = th > g.threads ? th : g.threads;  // (kind 0: from max_nx)
         g.max_nx = q.nx > g.max_nx ? q.nx : g.max_nx;
         g.max_rows = S.nsteps > g.max_rows ? S.nsteps : g.max_rows;
         g.max_ldp = S.ldp > g.max_ldp ? S.ldp : g.max_ldp;
@@ -394,6 +395,21 @@ void plan_batch(const mig_section* secs, int nsec, const mig_table_desc* d, cons
         });
         for (int si : order)
             for (int r0 = 0; r0 < g.secs[si].nw; r0 += g.secs[si].G) g.items.push_back(ItemDev{si, r0});
+        // Places for the reducers' tasks are kept in any case, so that the workspace does not
+        // depend on the device's CUs.
+        size_t ntasks = 0;
+        for (const SecDev& S : g.secs) ntasks += (size_t)blocks_of(S.nsteps) * parts_of(S.nx);
+        g.desc_bytes = g.secs.size() * sizeof(SecDev) + g.items.size() * sizeof(ItemDev) +
+                       ntasks * sizeof(TaskDev);
+        g.desc_off = bump(off, g.desc_bytes);
+        // Reducers where the caller asks for them, or the items leave them CUs, as for one
+        // section (run_extrap): beside more items than CUs there were 8 of them by
+        // default, which took longer over the rows than the rest of the launch (16 uneven
+        // sections of 256 to 2048 points: 18.7 -> 7.2 ms; 32 of them, an eighth of the
+        // CUs, come within a few percent of rows summed afterwards either way).
+        g.beside = tn.nred > 0 || tn.flags != 0 ||
+                   (k != 0 && device_cus() - (int)g.items.size() >= kReducerCus);
+        if (!g.beside) continue;
         g.nred = reducer_count((int)g.items.size(), tn.nred);
         g.parts = parts_of(g.secs[0].nx);  // read by a batch of one section only
         // Reducer tasks in the order their blocks are expected to be published
@@ -435,9 +451,6 @@ void plan_batch(const mig_section* secs, int nsec, const mig_table_desc* d, cons
                 g.tasks.push_back(TaskDev{b.sec, b.c, x0, x0 + span < nx ? x0 + span : nx});
             }
         }
-        g.desc_bytes = g.secs.size() * sizeof(SecDev) + g.items.size() * sizeof(ItemDev) +
-                       g.tasks.size() * sizeof(TaskDev);
-        g.desc_off = bump(off, g.desc_bytes);
     }
     P.bytes = align_up(off, kAlign);
 }
@@ -500,14 +513,7 @@ int run_batch(const mig_section* secs, int nsec, const float2* tab, const mig_ta
         set_reducer_limits(a, tn);
         a.nsec = (int)g.secs.size();
         a.nitems = (int)g.items.size();
-        // Reducers where the caller asks for them, or the items leave them CUs, as for one
-        // section (run_extrap): beside more items than CUs there were 8 of them by
-        // default, which took longer over the rows than the rest of the launch (16 uneven
-        // sections of 256 to 2048 points: 18.7 -> 7.4 ms; 32 of them, an eighth of the
-        // CUs, come within a few percent of rows summed afterwards either way).
-        const bool asked = tn.nred > 0 || tn.flags != 0;
-        const bool beside = asked || (g.kind != 0 && device_cus() - a.nitems >= kReducerCus);
-        a.ntasks = beside ? (int)g.tasks.size() : 0;
+        a.ntasks = (int)g.tasks.size();  // none where no reducers run
         a.nred = g.nred < a.ntasks ? g.nred : a.ntasks;
         a.rows = 1;
         // a batch of one section derives its tasks from `parts` (task_of) with
@@ -530,7 +536,7 @@ int run_batch(const mig_section* secs, int nsec, const float2* tab, const mig_ta
             if (g.kind == 0) rc = launch_general(a, g.max_nx, s);
             else rc = launch_extrap(a, g.kind, g.threads, false, s);
         }
-        if (rc == MIG_OK && !beside) rc = launch_rows_batch(a, g.max_nx, g.max_rows, s);
+        if (rc == MIG_OK && !g.beside) rc = launch_rows_batch(a, g.max_nx, g.max_rows, s);
         if (rc != MIG_OK) return rc;
     }
     return MIG_OK;
@@ -680,7 +686,7 @@ MIG_API int mig_extrapolate(const mig_c64* wf_in, mig_c64* wf_out, const float* 
     if (ws && (overlap(ws, ws_bytes, wf_in, pl) || (wf_out && overlap(ws, ws_bytes, wf_out, pl))))
         return MIG_E_ARG;
     return run_extrap(src, dst, vel, omega, reinterpret_cast<const float2*>(tab32), d, nx, nw,
-                      nsteps, rows, ws, ws_bytes, s, Tuning{});
+                      nsteps, rows, ws, ws_bytes, s);
 }
 
 MIG_API int mig_image(const mig_c64* wf, double* row, int32_t nx, int32_t nw, void* stream)
@@ -704,7 +710,7 @@ MIG_API int mig_migrate(const mig_c64* data, const float* vel, const double* ome
     if (ws && overlap(ws, ws_bytes, data, pl)) return MIG_E_ARG;
     return run_extrap(reinterpret_cast<const float2*>(data), nullptr, vel, omega,
                       reinterpret_cast<const float2*>(tab32), d, nx, nw, nz - 1, image + nx, ws,
-                      ws_bytes, s, Tuning{});
+                      ws_bytes, s);
 }
 
 MIG_API int mig_migrate_noalloc(const mig_c64* data, const float* vel, const double* omega,
@@ -857,7 +863,7 @@ MIG_API int mig_transform_t(const float* section, int32_t nx, int32_t nt, double
 }
 
 // Internal query used by tests and the benchmark: which extrapolation kernel
-// a call with these sizes takes (1 = register-tap kernel, 0 = general).
+// a call with these sizes takes.
 MIG_API int mig_kernel_kind(int32_t nx, int32_t ntaps)
 {
     if (ntaps < 1 || ntaps > MIG_MAX_NTAPS || (ntaps % 2) == 0 || nx < 1) return -1;

@@ -186,10 +186,10 @@ inline int row_stride(int nx) { return (nx + 255) / 256 * 256; }
 // 2 = register taps, four outputs per thread, one tap set (nx <= 2048);
 // 0 = general kernel (any size), taps in registers or read from the table by wave.
 int extrap_kernel_kind(int nx, int M);
-// Threads one frequency needs in kernel `kind` for nx points.
+// Threads one frequency needs in kernel `kind` (1, 2 or 3) for nx points.
 int threads_per_omega(int kind, int nx);
 // Kernel 1 with one output per thread, in a launch of one section, and its threads.
-bool extrap_narrow(int kind, int nx, int G, int nitems, int cus);
+bool extrap_narrow(int kind, int nx, int nitems, int cus);
 int threads_narrow(int nx);
 
 // Host launchers (return MIG_OK or MIG_E_DEVICE).

@@ -579,9 +579,10 @@ int extrap_kernel_kind(int nx, int M)
 // 257 -> 182 us, 290 frequencies: 270 -> 216 us.  Up to 512 points (eight waves) where
 // every workgroup has a CU to itself: 150 frequencies, 400 points: 261 -> 235 us, 512
 // points: 264 -> 242 us, but 290 frequencies of 450 points: 329 -> 374 us.
-bool extrap_narrow(int kind, int nx, int G, int nitems, int cus)
+// (A batch's launch holds sections of any of these widths and keeps to two.)
+bool extrap_narrow(int kind, int nx, int nitems, int cus)
 {
-    return kind == 1 && G * ((nx + 63) / 64 * 64) <= 512 && (nx <= 256 || nitems <= cus);
+    return kind == 1 && nx <= 512 && (nx <= 256 || nitems <= cus);
 }
 
 int threads_narrow(int nx) { return (nx + 63) / 64 * 64; }
@@ -590,8 +591,7 @@ int threads_per_omega(int kind, int nx)
 {
     if (kind == 1) return ((nx + 1) / 2 + 63) / 64 * 64;
     if (kind == 2) return ((nx + 3) / 4 + 63) / 64 * 64;
-    if (kind == 3) return ((nx + 2) / 3 + 63) / 64 * 64;
-    return 256;
+    return ((nx + 2) / 3 + 63) / 64 * 64;
 }
 
 int launch_slowness(const BatchArgs& a, int max_rows, int max_ldp, int dist, hipStream_t s)
