@@ -110,7 +110,9 @@ MIG_API const char* mig_strerror(int code);
 MIG_API const char* mig_version(void);
 
 /* Bytes of workspace mig_design_table needs for this descriptor (0 on a bad
- * descriptor). */
+ * descriptor): the bases on both grids, a status per entry, and 16 ngrid bytes
+ * of target values for each entry in flight, nk + 8 or 2048 of them (34 MB for
+ * a large table on the default grid). */
 MIG_API size_t mig_design_workspace_size(const mig_table_desc* d);
 
 /*
