@@ -135,7 +135,7 @@ __host__ __device__ constexpr int design_waves(int KT) { return KT <= 18 ? 1 : (
 // CU are put on the same SIMDs while the others idle (11 x 11 taps, 1024 entries: 8.75
 // ms); the four waves of one workgroup are spread over the four (6.15 ms: teams of two
 // waves then meet at the same barriers).  Where two teams of two waves per CU are all
-// there is, each wave asks for a SIMD of its own instead (5.79 ms; SOLO).
+// there is, each wave asks for a SIMD of its own instead (5.78 ms; SOLO).
 __host__ __device__ constexpr int design_teams(int KT) { return 4 / design_waves(KT); }
 
 constexpr int kDesignChunk = 64;  // grid points per chunk of the basis
@@ -327,11 +327,11 @@ __device__ __forceinline__ void design_fetch(v2f64 (&pre)[NV], v2f64 (&dpre)[NE]
 }
 
 // Bound by instruction issue (one wave per SIMD: about 6 cycles per FP64 operation).
-// 35 taps, 2048 entries: 16.0 -> 2.98 ms per table; 11 x 11 taps, 1024 entries: 28.4 ->
-// 5.79 ms; 63 taps, 2048 entries: 51.0 -> 9.1 ms (before: one workgroup per entry, a
+// 35 taps, 2048 entries: 16.0 -> 2.90 ms per table; 11 x 11 taps, 1024 entries: 28.4 ->
+// 5.78 ms; 63 taps, 2048 entries: 51.0 -> 9.1 ms (before: one workgroup per entry, a
 // thread per sum reading the basis from L2, the solves on one thread).  Of a pass of two
-// 35-tap entries the sums take 152 k of 232 k cycles, the solves 28 k, the responses
-// 25 k, the chunks' copies 13 k.
+// 35-tap entries the sums take 154 k of 224 k cycles, the solves 28 k, the responses
+// 27 k, the chunks' copies 12 k.
 //
 // Every instance keeps to 256 registers, without accumulation registers, spills or
 // scratch (tests/test_build_resources.py holds it to that): a build of this kernel that
@@ -352,11 +352,12 @@ k_design(DesignParams P, const double* __restrict__ A, const double* __restrict_
     constexpr int W = design_waves(KT), T = 64 * W, CH = kDesignChunk;
     constexpr int RS = design_stride(KT, EB), RP = RS / 2, LD = KT | 1;
     constexpr int DC = design_target_col(KT), WC = design_weight_col(KT, EB);
-    __shared__ double s_red_[design_teams(KT)][EB][W];
-    __shared__ int s_fail_[design_teams(KT)][EB];
+    constexpr int TM = SOLO ? 1 : design_teams(KT);  // teams of a workgroup, at most
+    __shared__ double s_red_[TM][EB][TM * W];
+    __shared__ int s_fail_[TM][EB];
     const int teams = blockDim.x / T, team = __builtin_amdgcn_readfirstlane(threadIdx.x / T);
     const int K = P.K, L = P.L, t = threadIdx.x - team * T, wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    double (&s_red)[EB][W] = s_red_[team];
+    double (&s_red)[EB][TM * W] = s_red_[team];
     int (&s_fail)[EB] = s_fail_[team];
     const int LL = TWO_D ? L * L : L, np = design_points(L, TWO_D);
     const DesignLds o = design_lds(L, KT, EB, TWO_D);
@@ -528,7 +529,7 @@ k_design(DesignParams P, const double* __restrict__ A, const double* __restrict_
                 // Few waves share a SIMD here, so the order is explicit: U grid points'
                 // operands are read while the U before them are summed, and each point's
                 // products stand apart from their sums.
-                constexpr int U = EB == 2 && W == 1 ? 3 : 4;  // (registers)
+                constexpr int U = EB == 2 && KT == 18 ? 3 : 4;  // (registers)
                 struct Ops {
                     v2f64 p, q;
                     double w[EB];
@@ -628,19 +629,39 @@ k_design(DesignParams P, const double* __restrict__ A, const double* __restrict_
 
         // Stability scale: |H|max <= max_grid |H| / cos(M pi / (2 Lc)) (in two dimensions
         // the bound applies along each axis, hence squared).
-        double g[EB], g2[EB];  // g2 screens points whose |H| cannot be the largest
-#pragma unroll
-        for (int e = 0; e < EB; ++e) g[e] = g2[e] = 0.0;
-        auto raise = [&](int e, double Hr, double Hi) {
+        // g2 screens points whose |H| cannot be the largest.
+        auto raise = [&](double& g, double& g2, double Hr, double Hi) {
             const double s2 = Hr * Hr + Hi * Hi;
-            if (!(s2 < g2[e])) {
-                g[e] = fmax(g[e], hypot(Hr, Hi));
-                g2[e] = s2 * (1.0 - 1e-12);
+            if (!(s2 < g2)) {
+                g = fmax(g, hypot(Hr, Hi));
+                g2 = s2 * (1.0 - 1e-12);
             }
         };
+        auto wave_max = [&](double v) {
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
+            return v;
+        };
+        auto block_max = [&](double (&v)[EB]) {
+#pragma unroll
+            for (int e = 0; e < EB; ++e) {
+                v[e] = wave_max(v[e]);
+                if ((t & 63) == 0) s_red[e][t >> 6] = v[e];
+            }
+            team_sync<W>();
+#pragma unroll
+            for (int e = 0; e < EB; ++e)
+#pragma unroll
+                for (int q = 0; q < W; ++q) v[e] = fmax(v[e], s_red[e][q]);
+            team_sync<W>();
+        };
+        double g[EB];
+#pragma unroll
+        for (int e = 0; e < EB; ++e) g[e] = 0.0;
         if constexpr (TWO_D) {
             // |H| is symmetric: points with q <= i
             const int Lc = P.Lc, M = P.M;
+            double g2[EB] = {};
             for (int x = t; x < Lc * Lc; x += T) {
                 const int i = x / Lc, q = x - i * Lc;
                 if (q > i) continue;
@@ -667,59 +688,68 @@ k_design(DesignParams P, const double* __restrict__ A, const double* __restrict_
                         }
                     }
 #pragma unroll
-                for (int e = 0; e < EB; ++e) raise(e, Hr[e], Hi[e]);
+                for (int e = 0; e < EB; ++e) raise(g[e], g2[e], Hr[e], Hi[e]);
             }
+            block_max(g);
         } else {
-            // a point's basis values are asked for while the point before is evaluated
-            // (where registers allow)
-            constexpr bool ahead = KT <= 24;
-            double cc[KT];
-            const auto get = [&](double (&v)[KT], int c) {
+            // The workgroup's teams share the points, and each point's basis values serve the
+            // entries of all: each team reading the whole basis, some waited for it four
+            // times as long as the arithmetic takes (35 taps, 2048 entries, in all 2.98 ->
+            // 2.90 ms).  NP points at a time share the reads of the coefficients.
+            constexpr int NP = KT <= 18 ? 2 : 1;
+            double ga[TM][EB] = {}, g2[TM][EB] = {};
+            __syncthreads();  // every team's coefficients
+            for (int c = threadIdx.x; c < P.Lc; c += NP * blockDim.x) {
                 int Kc = K;
                 asm volatile("" : "+s"(Kc));  // (hoisted, the rows' offsets would fill the scalar registers)
+                double cc[NP][KT];
 #pragma unroll
-                for (int q = 1; q < KT; ++q) v[q] = C[(size_t)(q < Kc ? q : 0) * P.Lc + c];
-            };
-            if (ahead) get(cc, t < P.Lc ? t : 0);
-            for (int c = t; c < P.Lc; c += T) {
-                double next[KT];
-                if (ahead) get(next, c + T < P.Lc ? c + T : c);
-                else get(cc, c);
+                for (int u = 0; u < NP; ++u) {
+                    const int at = c + u * blockDim.x < P.Lc ? c + u * blockDim.x : c;  // past the grid: again
 #pragma unroll
-                for (int e = 0; e < EB; ++e) {
-                    double Hr = hs[e * KT].x, Hi = hs[e * KT].y;
-#pragma unroll
-                    for (int q = 1; q < KT; ++q) {  // coefficients past K are zero
-                        const v2f64 hv = hs[e * KT + q];
-                        Hr += cc[q] * hv.x;
-                        Hi += cc[q] * hv.y;
-                        if (q % 8 == 7) {
-                            asm volatile("" : "+v"(Hr), "+v"(Hi));
-                            __builtin_amdgcn_sched_barrier(0);
-                        }
-                    }
-                    raise(e, Hr, Hi);
+                    for (int q = 1; q < KT; ++q) cc[u][q] = C[(size_t)(q < Kc ? q : 0) * P.Lc + at];
                 }
 #pragma unroll
-                for (int q = 1; q < KT; ++q)
-                    if (ahead) cc[q] = next[q];
-            }
-        }
-        auto block_max = [&](double (&v)[EB]) {
+                for (int m = 0; m < TM; ++m) {
+                    if (m >= teams) break;
+                    const v2f64* const ht = smem2 + m * (o.total / 2) + o.h / 2;
 #pragma unroll
-            for (int e = 0; e < EB; ++e) {
+                    for (int e = 0; e < EB; ++e) {
+                        double Hr[NP], Hi[NP];
 #pragma unroll
-                for (int off = 32; off >= 1; off >>= 1) v[e] = fmax(v[e], __shfl_xor(v[e], off, 64));
-                if ((t & 63) == 0) s_red[e][t >> 6] = v[e];
+                        for (int u = 0; u < NP; ++u) {
+                            Hr[u] = ht[e * KT].x;
+                            Hi[u] = ht[e * KT].y;
+                        }
+#pragma unroll
+                        for (int q = 1; q < KT; ++q) {  // coefficients past K are zero
+                            const v2f64 hv = ht[e * KT + q];
+#pragma unroll
+                            for (int u = 0; u < NP; ++u) {
+                                Hr[u] += cc[u][q] * hv.x;
+                                Hi[u] += cc[u][q] * hv.y;
+                                if (q % 8 == 7) asm volatile("" : "+v"(Hr[u]), "+v"(Hi[u]));
+                            }
+                            if (q % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+                        }
+#pragma unroll
+                        for (int u = 0; u < NP; ++u) raise(ga[m][e], g2[m][e], Hr[u], Hi[u]);
+                    }
+                }
             }
-            team_sync<W>();
+#pragma unroll
+            for (int m = 0; m < TM; ++m)
+#pragma unroll
+                for (int e = 0; e < EB; ++e) {
+                    const double v = wave_max(ga[m][e]);
+                    if ((threadIdx.x & 63) == 0) s_red_[m][e][threadIdx.x >> 6] = v;
+                }
+            __syncthreads();
 #pragma unroll
             for (int e = 0; e < EB; ++e)
-#pragma unroll
-                for (int q = 0; q < W; ++q) v[e] = fmax(v[e], s_red[e][q]);
+                for (int q = 0; q < teams * W; ++q) g[e] = fmax(g[e], s_red[e][q]);
             team_sync<W>();
-        };
-        block_max(g);
+        }
         const double cb = cos((double)P.M * kPi / (2.0 * (double)P.Lc));
         const double lim = TWO_D ? (1.0 - P.margin) * cb * cb : (1.0 - P.margin) * cb;
         double s[EB], perr[EB];
