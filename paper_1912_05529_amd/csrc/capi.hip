@@ -405,8 +405,9 @@ void plan_batch(const mig_section* secs, int nsec, const mig_table_desc* d, cons
         // Reducers where the caller asks for them, or the items leave them CUs, as for one
         // section (run_extrap): beside more items than CUs there were 8 of them by
         // default, which took longer over the rows than the rest of the launch (16 uneven
-        // sections of 256 to 2048 points: 18.7 -> 7.2 ms; 32 of them, an eighth of the
-        // CUs, come within a few percent of rows summed afterwards either way).
+        // sections of 256 to 2048 points: 18.7 -> 7.0 ms; 32 of them, an eighth of the
+        // CUs, come within a few percent of rows summed afterwards either way).  No rule
+        // on the size of the rows as there: a launch holds sections of many.
         g.beside = tn.nred > 0 || tn.flags != 0 ||
                    (k != 0 && device_cus() - (int)g.items.size() >= kReducerCus);
         if (!g.beside) continue;

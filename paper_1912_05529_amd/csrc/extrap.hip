@@ -97,7 +97,7 @@ __global__ void k_slowness(BatchArgs a, int dist)
 // busy for 16 clocks however many lanes ask and wherever the rows are cached, and a wave
 // waits until its loads are accepted.  As one masked block before the FIR they took 155 of
 // 575 us at 1024 points, 512 depths, 200 frequencies, layered, and 165 of 420 us at 601
-// points, 301 depths, 97 frequencies where every point changes at every step (now 514 and
+// points, 301 depths, 97 frequencies where every point changes at every step (now 487 and
 // 335 in all).
 template <int Q>
 struct Refill {
