@@ -529,7 +529,7 @@ k_design(DesignParams P, const double* __restrict__ A, const double* __restrict_
                 // Few waves share a SIMD here, so the order is explicit: U grid points'
                 // operands are read while the U before them are summed, and each point's
                 // products stand apart from their sums.
-                constexpr int U = EB == 2 && KT == 18 ? 3 : 4;  // (registers)
+                constexpr int U = 4;
                 struct Ops {
                     v2f64 p, q;
                     double w[EB];
@@ -695,8 +695,9 @@ k_design(DesignParams P, const double* __restrict__ A, const double* __restrict_
             // The workgroup's teams share the points, and each point's basis values serve the
             // entries of all: each team reading the whole basis, some waited for it four
             // times as long as the arithmetic takes (35 taps, 2048 entries, in all 2.98 ->
-            // 2.90 ms).  NP points at a time share the reads of the coefficients.
-            constexpr int NP = KT <= 18 ? 2 : 1;
+            // 2.90 ms).  NP points at a time share the reads of the coefficients
+            // (where registers allow).
+            constexpr int NP = KT <= 12 || (KT <= 18 && EB == 1) ? 2 : 1;
             double ga[TM][EB] = {}, g2[TM][EB] = {};
             __syncthreads();  // every team's coefficients
             for (int c = threadIdx.x; c < P.Lc; c += NP * blockDim.x) {
