@@ -21,7 +21,8 @@
 //     k, by waves some output of which changes its slowness.  The loads stand
 //     between the stages of the FIR, whose arithmetic hides them; the slowness
 //     is read two steps ahead, and a partial row is stored at the end of its
-//     step and first waited for a step later.
+//     step (three and four outputs: at the start of the next) and first waited
+//     for a step later.
 //   * The look-up needs 1/v in FP64; it is computed once per (depth, x) by a
 //     small pre-pass (shared by all frequencies) instead of once per refill.
 //   * The image row needs a sum over frequencies, i.e. across workgroups.
